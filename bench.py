@@ -88,8 +88,8 @@ def parse():
 
 
 # the bf16 conv launches (trace class conv_mfma): the GEMM kernel and the direct conv kernel
-CONV_SOURCES = [os.path.join(ROOT, "paper_1804_06087_amd", "csrc", f) for f in ("conv_mfma.hip", "conv_direct.hip")]
-CONV_KERNEL_NAMES = ("conv_mfma_kernel", "conv_direct_kernel")
+CONV_SOURCES = [os.path.join(ROOT, "paper_1804_06087_amd", "csrc", f) for f in ("conv_mfma.hip", "conv_direct.hip", "bottleneck.hip")]
+CONV_KERNEL_NAMES = ("conv_mfma_kernel", "conv_direct_kernel", "block_kernel")
 
 
 def strip_comments(src: str) -> str:
@@ -649,7 +649,8 @@ def layers_main(args, dev):
             desc = f"{OP_NAMES[L.op]} {L.c_in}->{L.c_out} {L.kh}x{L.kw}/{L.stride}"
             if OP_NAMES[L.op] == "concat" and kind != "concat":   # branches fused into one GEMM + max
                 desc = f"conv1d_maxtime branches -> concat {L.c_out}"
-        tile = ("direct" if a["cfg"] == n_gemm_cfgs else f"{a['cfg']} / {a['splits']}") if a["cfg"] >= 0 else ""
+        special = {n_gemm_cfgs: "direct", n_gemm_cfgs + 1: "block 64", n_gemm_cfgs + 2: "block 32"}
+        tile = special.get(a["cfg"], f"{a['cfg']} / {a['splits']}") if a["cfg"] >= 0 else ""
         print(f"| {specs[m].name if m >= 0 else '-'} | {li} | {desc} | {kind} | {tile} | {a['ms'] * 1e3:.1f} | "
               f"{a['flops'] / a['ms'] / 1e9:.0f} | {a['bytes'] / a['ms'] / 1e6:.0f} | {bound} | {tb * 1e3:.1f} | "
               f"{tb / a['ms']:.2f} |")

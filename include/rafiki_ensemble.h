@@ -121,7 +121,12 @@ typedef struct {
  * n_classes.  Validates the layer lists, folds batch-norm into a per-channel fp32
  * scale and shift (computed in fp64), rounds weights to the compute precision,
  * packs them for the kernels, uploads them synchronously to the current device and
- * sizes the workspace for opts->max_batch.  In bf16, conv1d max-over-time layers that
+ * sizes the workspace for opts->max_batch.  In bf16, consecutive bottleneck layers (3x3
+ * stride 1 over 64, 128 or 256 channels, 1x1 expansion to four times as many with
+ * residual, the next block's 1x1 reduction; all with ReLU) may run as one launch, which
+ * the tuner times against the layers apart; outputs are bitwise the same (environment
+ * RAFIKI_FUSED_BLOCKS at create: 0 always apart, 32 or 64 always fused with that many
+ * pixels per workgroup).  Also in bf16, conv1d max-over-time layers that
  * read one sequence and whose outputs are joined only by concatenations (the TextCNN's
  * kernel widths) are packed as one GEMM whose max over time writes the concatenated
  * vector; every output value is that of its own layer's sum of products (environment
@@ -211,7 +216,10 @@ typedef struct {
                                    (hipExtLaunchKernelGGL start/stop events) */
   int tile_cfg;                 /* bf16 GEMM launches (conv_mfma, splitk_reduce): the tile
                                    configuration used (rafiki_tile_config), or the number of
-                                   configurations for the direct conv kernel; -1 otherwise */
+                                   configurations for the direct conv kernel, that plus 1 or
+                                   2 for a layer of a fused bottleneck launch of 64 or 32
+                                   pixels per workgroup (such a launch has one record per
+                                   layer, its time split by their FLOPs); -1 otherwise */
   int splits;                   /* the same launches: K splits (1 = unsplit); 0 otherwise */
 } rafiki_trace_rec;
 

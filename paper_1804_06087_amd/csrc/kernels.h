@@ -263,6 +263,30 @@ struct FusedNetArgs {
 };
 hipError_t launch_fused_net(const FusedNetArgs& a, int n, int n_models, hipStream_t s);
 
+// Fused bottleneck block (bottleneck.hip): over M pixels of H x W maps, MID channels,
+//   [3x3 stride 1 pad 1, MID -> MID, ReLU;] 1x1 MID -> 4 MID + residual, ReLU -> y;
+//   [1x1 4 MID -> MID, ReLU -> z], all bf16 NHWC with folded scale / shift.
+struct BlockArgs {
+  const void* x;       // [M][MID]: input of the 3x3 (has_b) or its output
+  const void* res;     // residual [M][4 MID]
+  void* y;             // [M][4 MID]
+  void* z;             // [M][MID], or nullptr: no reduction
+  const void* w;       // weights in the waves' order (launch_pack_block_weights)
+  const float* table;  // (scale, shift) pairs: [MID] of the 3x3 (has_b), [4 MID], [MID] (z)
+  int x_bytes, y_bytes, w_bytes, w_wave_bytes;
+  int M, H, W, has_b;
+  int b_per, a_per;    // K tiles of 64 per partial sum of the 3x3 and of the reduction
+};
+// A map of MID channels may be at most kBlockRowBytes / MID pixels wide (the 3x3's patch
+// of a tile and its halo then fits in LDS).
+constexpr int kBlockRowBytes = 3584;
+size_t block_weight_bytes(int mid, bool has_b, bool has_a);
+// Packs weights [rows][kp] of the three layers (wb, wa may be null) for block_kernel.
+hipError_t launch_pack_block_weights(const bf16_t* wb, int kpb, const bf16_t* wc, int kpc, const bf16_t* wa, int kpa,
+                                     int mid, bf16_t* out, hipStream_t s);
+// bm: pixels per workgroup, 32 or 64.
+hipError_t launch_block(const BlockArgs& a, int mid, int bm, hipStream_t s);
+
 // Peak probes: register-resident bf16 MFMA loop (out [blocks * 4] checksums) and a
 // streaming 16-byte read of words16 words (out [blocks * 4]).
 hipError_t launch_probe_mfma(int blocks, int iters, float* out, hipStream_t s);

@@ -94,9 +94,21 @@ struct Op {
   int ca = 0, cb = 0;
 };
 
+// Consecutive ops of a model that may run as one fused bottleneck launch (bottleneck.hip):
+// ops [first, last] are [3x3,] 1x1 expansion with residual [, the next block's 1x1 reduction].
+struct BlockUnit {
+  int first = 0, last = 0;
+  int b = -1, c = -1, a = -1;   // op indices of the 3x3, the expansion and the reduction (-1: none)
+  int mid = 0;
+  void* d_w = nullptr;          // weights in the kernel's order
+  float* d_table = nullptr;     // (scale, shift) pairs of the three layers
+};
+
 struct Model {
   std::vector<Op> ops;
   std::vector<Tensor> tensors;
+  std::vector<BlockUnit> units;
+  std::vector<int> unit_of;       // per op: its unit, or -1
   char* d_arena = nullptr;
   size_t arena_bytes = 0;
   float* d_partial = nullptr;     // split-K partial sums (per model: models may run concurrently)
@@ -147,7 +159,8 @@ struct FreeList {
 struct Tracer {
   bool on = false;
   bool concurrent = false;   // keep the models' own streams and schedule while tracing
-  struct Rec { int kind, model, layer; double flops, bytes; hipEvent_t a, b; int tile_cfg, splits; };
+  // share: the record's part of the launch's time (a fused launch has one record per layer)
+  struct Rec { int kind, model, layer; double flops, bytes; hipEvent_t a, b; int tile_cfg, splits; float share = 1.f; };
   std::vector<Rec> recs;
   std::vector<hipEvent_t> pool;
   size_t used = 0;
@@ -188,6 +201,12 @@ struct rafiki_ensemble_s {
   // the direct kernel's persistent workgroups fill each compute unit's LDS, which leaves
   // no room for the other lane's workgroups while it runs.
   std::map<int, std::vector<std::vector<int>>> tuned_lean_gemm;
+  // Per batch size, model and block unit: pixels per workgroup of its fused launch (0: the
+  // layers run apart), whichever was faster when tuning.
+  std::map<int, std::vector<std::vector<int>>> blocks;
+  // RAFIKI_FUSED_BLOCKS at create: 0 the layers always apart, 1 the faster when tuning, 32 or
+  // 64 always fused with that many pixels per workgroup
+  int fused_blocks = 1;
   // Per batch size: each model's forward time alone, estimated when tuning (sum of the
   // chosen tiles' times; GEMM FLOPs / 1e12 when tiles are not timed).
   std::map<int, std::vector<double>> model_ms;
@@ -552,6 +571,76 @@ int fuse_branches(rafiki_ensemble_s* e, const rafiki_model_desc& md, Model& M, c
   return RAFIKI_OK;
 }
 
+// The units of model M that the fused bottleneck kernel can run (bf16): a 1x1 expansion from
+// mid = 64, 128 or 256 to 4 mid channels with residual and ReLU, preceded by the 3x3 stride-1
+// convolution that only it reads, or followed by a 1x1 reduction of its output to mid channels,
+// or both, as consecutive ops.  Maps may be at most kBlockRowBytes / mid pixels wide with a 3x3
+// (its patch must fit in LDS).  Packs their weights unless the handle is in its validation pass.
+int find_blocks(rafiki_ensemble_s* e, const rafiki_model_desc& md, Model& M) {
+  M.units.clear();
+  M.unit_of.assign(M.ops.size(), -1);
+  if (e->precision != RAFIKI_BF16 || !e->fused_blocks) return RAFIKI_OK;
+  std::vector<int> readers(M.tensors.size(), 0);
+  for (const Op& op : M.ops)
+    for (int src : {op.in, op.in2})
+      if (src >= 0) ++readers[src];
+  // a ReLU convolution k x k, stride 1, "same" padding, from cin to cout channels stored unpadded
+  auto conv = [&](const Op& op, int k, int cin, int cout) {
+    const Tensor& y = M.tensors[op.out];
+    return op.kind == O_CONV && op.nseg == 0 && !op.table && !op.pool2 && op.kh == k && op.kw == k && op.stride == 1 &&
+           op.pad == k / 2 && op.relu && op.cin_l == cin && op.Cs_in == cin && op.c_out == cout && y.kind == T_IMG &&
+           y.Cs == cout && !y.is_logits && op.in >= 0;
+  };
+  for (int i = 0; i < (int)M.ops.size(); ++i) {
+    const Op& C = M.ops[i];
+    const int mid = C.Cs_in;
+    if ((mid != 64 && mid != 128 && mid != 256) || !conv(C, 1, mid, 4 * mid) || C.in2 < 0 || C.in2 == C.in) continue;
+    if ((long long)e->max_batch * C.Ho * C.Wo * 4 * mid * 2 >= (1LL << 31)) continue;   // 32-bit offsets
+    BlockUnit u;
+    u.c = u.first = u.last = i;
+    u.mid = mid;
+    if (i > 0 && M.unit_of[i - 1] < 0) {
+      const Op& B = M.ops[i - 1];
+      if (B.out == C.in && readers[B.out] == 1 && B.in2 < 0 && conv(B, 3, mid, mid) && B.W <= kBlockRowBytes / mid &&
+          B.in != C.in2)
+        u.b = u.first = i - 1;
+    }
+    if (i + 1 < (int)M.ops.size()) {
+      const Op& A = M.ops[i + 1];
+      if (A.in == C.out && A.in2 < 0 && conv(A, 1, 4 * mid, mid)) u.a = u.last = i + 1;
+    }
+    if (u.first == u.last) continue;
+    for (int k = u.first; k <= u.last; ++k) M.unit_of[k] = (int)M.units.size();
+    M.units.push_back(u);
+  }
+  if (e->dry) return RAFIKI_OK;
+  for (BlockUnit& u : M.units) {
+    const Op* ops[3] = {u.b >= 0 ? &M.ops[u.b] : nullptr, &M.ops[u.c], u.a >= 0 ? &M.ops[u.a] : nullptr};
+    std::vector<float> table;
+    for (const Op* op : ops) {
+      if (!op) continue;
+      std::vector<float> sc(op->c_out), sh(op->c_out);
+      fold_into(md.layers[op->out], sc.data(), sh.data());
+      for (int c = 0; c < op->c_out; ++c) {
+        table.push_back(sc[c]);
+        table.push_back(sh[c]);
+      }
+    }
+    int rc = upload(e, (void**)&u.d_table, table.data(), table.size() * 4);
+    if (!rc) rc = dev_alloc(e, &u.d_w, block_weight_bytes(u.mid, u.b >= 0, u.a >= 0));
+    if (rc) return rc;
+    const hipError_t st = launch_pack_block_weights(
+        ops[0] ? (const bf16_t*)ops[0]->d_w : nullptr, ops[0] ? ops[0]->Kp : 0, (const bf16_t*)ops[1]->d_w, ops[1]->Kp,
+        ops[2] ? (const bf16_t*)ops[2]->d_w : nullptr, ops[2] ? ops[2]->Kp : 0, u.mid, (bf16_t*)u.d_w, nullptr);
+    if (st != hipSuccess) return fail(RAFIKI_ERR_HIP, std::string("packing block weights: ") + hipGetErrorString(st));
+  }
+  if (!M.units.empty()) {
+    const hipError_t st = hipStreamSynchronize(nullptr);
+    if (st != hipSuccess) return fail(RAFIKI_ERR_HIP, std::string("packing block weights: ") + hipGetErrorString(st));
+  }
+  return RAFIKI_OK;
+}
+
 // Validate one model, infer shapes, build its ops and upload its parameters.
 int build_model(rafiki_ensemble_s* e, int mi, const rafiki_model_desc& md, Model& M) {
   if (md.n_layers < 1 || !md.layers) return fail(RAFIKI_ERR_INVALID, "model " + std::to_string(mi) + ": no layers");
@@ -776,11 +865,18 @@ int build_model(rafiki_ensemble_s* e, int mi, const rafiki_model_desc& md, Model
     M.ops.swap(ops);
   }
 
+  int brc = find_blocks(e, md, M);
+  if (brc) return brc;
+
   // Liveness-planned arena for max_batch requests (the logits go to the ensemble's slots);
-  // a tensor's last use is the index of the last op that reads it.
+  // a tensor's last use is the index of the last op that reads it.  A fused block reads its
+  // inputs while it writes every one of its outputs, so its inputs live to its last op.
   for (size_t i = 0; i < M.ops.size(); ++i)
     for (int src : {M.ops[i].in, M.ops[i].in2})
-      if (src >= 0) M.tensors[src].last_use = std::max(M.tensors[src].last_use, (int)i);
+      if (src >= 0) {
+        const int u = M.unit_of[i];
+        M.tensors[src].last_use = std::max(M.tensors[src].last_use, u >= 0 ? M.units[u].last : (int)i);
+      }
   FreeList fl;
   const size_t es = e->esz(), nb = (size_t)e->max_batch;
   for (size_t i = 0; i < M.ops.size(); ++i) {
@@ -1095,6 +1191,11 @@ int& lean_gemm_model() {
   return m;
 }
 
+// Tile ids beyond the GEMM's and the direct kernel's: fused bottleneck launches of 64 and 32
+// pixels per workgroup, and (in the tuner's records only) a split-K reduce launch.
+constexpr int kCfgBlock64 = kCfgDirect + 1, kCfgBlock32 = kCfgDirect + 2, kCfgReduce = kCfgDirect + 3;
+constexpr int kBlockTiles[2] = {64, 32};
+
 // A tile of the lean set: 8 waves, at least 128 x 128, K tiles of 64 (one barrier per 64
 // of K; the 32-wide tiles of the same footprint gained a third as much alongside other
 // models) and a ring of at most 64 KB.
@@ -1112,7 +1213,7 @@ bool lean_cfg(int cfg) {
       ta_ = (e)->trace.next();                                                                \
       tb_ = (e)->trace.next();                                                                \
       if (ta_ && tb_) launch_events() = {ta_, tb_};                                           \
-    } else if ((kind) == RAFIKI_K_CONV_MFMA && tune_probe()) {                                \
+    } else if (((kind) == RAFIKI_K_CONV_MFMA || (kind) == RAFIKI_K_SPLITK_REDUCE) && tune_probe()) { \
       pa_ = tune_probe()->next();                                                             \
       pb_ = tune_probe()->next();                                                             \
       if (pa_ && pb_) launch_events() = {pa_, pb_};                                           \
@@ -1120,7 +1221,8 @@ bool lean_cfg(int cfg) {
     const hipError_t lst_ = (expr);                                                           \
     launch_events() = {};                                                                     \
     HIPCHK(lst_);                                                                             \
-    if (pa_ && pb_) tune_probe()->recs.push_back({(layer), trace_tile().cfg, pa_, pb_});      \
+    if (pa_ && pb_)                                                                           \
+      tune_probe()->recs.push_back({(layer), (kind) == RAFIKI_K_CONV_MFMA ? trace_tile().cfg : kCfgReduce, pa_, pb_}); \
     if (ta_ && tb_)                                                                           \
       (e)->trace.recs.push_back({kind, model, layer, (double)(flops), (double)(bytes), ta_, tb_,     \
                                  trace_tile().cfg, trace_tile().splits});                           \
@@ -1159,6 +1261,63 @@ int check_limits(const rafiki_ensemble_s* e, int mi, const Model& M) {
   return RAFIKI_OK;
 }
 
+// K tiles of 64 per split of a GEMM over `rows` output rows.
+int kt_per_split(const Op& op, int rows) {
+  const int ktiles = op.Kp / 64, splits = choose_splits(rows, op.c_out, ktiles);
+  return (ktiles + splits - 1) / splits;
+}
+
+// One fused launch of unit u of model mi over n requests, bm pixels per workgroup.  It
+// needs no split-K workspace: the kernel keeps the partial sums the shape asks for apart in
+// registers.  Traced as one record per layer, the launch's time split by their FLOPs.
+int run_block(const rafiki_ensemble_s* e, int mi, const BlockUnit& u, int n, int bm, hipStream_t s) {
+  const Model& M = e->models[mi];
+  const Op& C = M.ops[u.c];
+  const Op& F = M.ops[u.first];
+  BlockArgs a{};
+  a.M = n * C.Ho * C.Wo;
+  a.H = C.H; a.W = C.W; a.has_b = u.b >= 0;
+  a.x = M.d_arena + M.tensors[F.in].off;
+  a.res = M.d_arena + M.tensors[C.in2].off;
+  a.y = M.d_arena + M.tensors[C.out].off;
+  a.z = u.a >= 0 ? M.d_arena + M.tensors[M.ops[u.a].out].off : nullptr;
+  a.w = u.d_w;
+  a.table = u.d_table;
+  a.x_bytes = a.M * u.mid * 2;
+  a.y_bytes = a.M * 4 * u.mid * 2;
+  a.w_bytes = (int)block_weight_bytes(u.mid, u.b >= 0, u.a >= 0);
+  a.w_wave_bytes = a.w_bytes / (u.mid / 32);
+  a.b_per = u.b >= 0 ? kt_per_split(M.ops[u.b], a.M) : 1;
+  a.a_per = u.a >= 0 ? kt_per_split(M.ops[u.a], a.M) : 1;
+  const int cfg = bm == 64 ? kCfgBlock64 : kCfgBlock32;
+  hipEvent_t ea = nullptr, eb = nullptr;
+  TuneProbe* probe = e->trace.on ? nullptr : tune_probe();
+  if (e->trace.on) {
+    ea = e->trace.next();
+    eb = e->trace.next();
+  } else if (probe) {
+    ea = probe->next();
+    eb = probe->next();
+  }
+  if (ea && eb) launch_events() = {ea, eb};
+  const hipError_t st = launch_block(a, u.mid, bm, s);
+  launch_events() = {};
+  HIPCHK(st);
+  if (ea && eb && probe) probe->recs.push_back({C.out, cfg, ea, eb});
+  if (ea && eb && e->trace.on) {
+    double total = 0.0;
+    for (int pass = 0; pass < 2; ++pass)
+      for (int k = u.first; k <= u.last; ++k) {
+        const Op& op = M.ops[k];
+        const double w = (double)op.c_out * op.kh * op.kw * op.cin_l, flops = 2.0 * a.M * w;
+        const double bytes = 2.0 * ((double)a.M * op.cin_l + w + (double)a.M * op.c_out * (op.in2 >= 0 ? 2 : 1));
+        if (pass == 0) total += flops;
+        else e->trace.recs.push_back({RAFIKI_K_CONV_MFMA, mi, op.out, flops, bytes, ea, eb, cfg, 1, (float)(flops / total)});
+      }
+  }
+  return RAFIKI_OK;
+}
+
 int run_gemm(const rafiki_ensemble_s* e, const Op& op, ConvArgs a, hipStream_t s, int mi, int li, int cfg,
              const CallScratch* ws = nullptr, const int* mis = nullptr) {
   const int nm = a.n_members > 1 ? a.n_members : 1;   // grouped launch: members mis[0 .. nm)
@@ -1189,7 +1348,7 @@ int run_gemm(const rafiki_ensemble_s* e, const Op& op, ConvArgs a, hipStream_t s
     return fail(RAFIKI_ERR_UNSUPPORTED, "a layer's input or weights exceed 2 GiB; use a smaller max_batch");
   const int ktiles = a.Kp / 64;
   int splits = choose_splits(a.M, op.c_out, ktiles);
-  a.kt_per_split = (ktiles + splits - 1) / splits;
+  a.kt_per_split = kt_per_split(op, a.M);
   if (a.tap_stride > 0 && splits > 1) {
     // fused branches: a split takes whole channel blocks, each with the taps of the
     // tile, so that every row's products fall into the same splits whatever the tile
@@ -1278,6 +1437,74 @@ inline int run_model(const rafiki_ensemble_s* e, int mi, const void* in, int n, 
   return run_models(e, &mi, 1, in, n, &logits, s, op_begin, op_end, ws);
 }
 
+// Fused or apart, for each block unit at batch size n: the fused launch with 64 and with 32
+// pixels per workgroup, timed like the tiles inside forward passes, against its layers'
+// fastest launches (`best`) with their split-K reduces.  Each launch saved counts
+// kLaunchGapMs, the time between two dependent launches of a stream beyond their own
+// execution (a chain of empty launches takes 2.6 us each, of which about 1 us is execution).
+// Updates the models' estimated times `est`.
+constexpr float kLaunchGapMs = 0.0015f;
+int tune_blocks(rafiki_ensemble_s* e, int n, const void* in, hipStream_t s,
+                const std::vector<std::vector<std::vector<float>>>& best, std::vector<double>& est) {
+  const size_t NM = e->models.size();
+  std::vector<std::vector<int>> pick(NM);
+  TuneProbe probe;
+  int rc = RAFIKI_OK;
+  const int saved_force = e->force_tile;
+  const bool saved_trace = e->trace.on;
+  e->force_tile = -1;
+  e->trace.on = false;
+  for (size_t mi = 0; mi < NM && rc == RAFIKI_OK; ++mi) {
+    const Model& M = e->models[mi];
+    pick[mi].assign(M.units.size(), 0);
+    if (M.units.empty()) continue;
+    std::vector<std::vector<float>> t(M.units.size(), std::vector<float>(2, 1e30f));
+    float* logits = e->d_logits + mi * (size_t)e->max_batch * e->n_classes;
+    for (int pass = 0; pass < 4 && rc == RAFIKI_OK; ++pass) {
+      const int v = pass & 1;
+      auto& all = e->blocks[n];
+      all.assign(NM, {});
+      all[mi].assign(M.units.size(), kBlockTiles[v]);
+      probe.recs.clear();
+      probe.used = 0;
+      tune_probe() = &probe;
+      rc = run_model(e, (int)mi, in, n, logits, s, 0, SIZE_MAX);
+      tune_probe() = nullptr;
+      for (size_t k = 0; k < probe.recs.size() && rc == RAFIKI_OK; ++k) {
+        const TuneProbe::Rec& r = probe.recs[k];
+        if (r.cfg != kCfgBlock64 && r.cfg != kCfgBlock32) continue;
+        float ms = 0.f;
+        hipError_t st = hipEventSynchronize(r.b);
+        if (st == hipSuccess) st = hipEventElapsedTime(&ms, r.a, r.b);
+        if (st != hipSuccess) rc = fail(RAFIKI_ERR_HIP, std::string("block timing: ") + hipGetErrorString(st));
+        for (size_t u = 0; u < M.units.size(); ++u)
+          if (M.ops[M.units[u].c].out == r.layer) t[u][v] = std::min(t[u][v], ms);
+      }
+    }
+    if (rc == RAFIKI_OK && hipStreamSynchronize(s) != hipSuccess) rc = fail(RAFIKI_ERR_HIP, "block timing");
+    for (size_t u = 0; u < M.units.size(); ++u) {
+      float conv = 0.f, apart = -kLaunchGapMs;
+      for (int k = M.units[u].first; k <= M.units[u].last; ++k) {
+        const Op& op = M.ops[k];
+        const float c = best[mi][k][e->tuned[n][mi][k]];
+        conv += c;
+        apart += c + kLaunchGapMs;
+        if (choose_splits(n * op.Ho * op.Wo, op.c_out, op.Kp / 64) > 1) apart += best[mi][k][kCfgReduce] + kLaunchGapMs;
+      }
+      int v = t[u][1] < t[u][0] ? 1 : 0;
+      if (e->fused_blocks > 1) v = e->fused_blocks == kBlockTiles[1] ? 1 : 0;
+      else if (t[u][v] >= apart) continue;
+      pick[mi][u] = kBlockTiles[v];
+      est[mi] += t[u][v] - conv;
+    }
+  }
+  e->force_tile = saved_force;
+  e->trace.on = saved_trace;
+  e->blocks.erase(n);
+  if (rc == RAFIKI_OK) e->blocks[n] = std::move(pick);
+  return rc;
+}
+
 // Choose each GEMM op's tile configuration for batch size n (once per n; blocks the
 // caller).  The candidates are timed where they will run: inside forward passes of
 // the model on stream s, one model at a time.  Pass j gives every GEMM op its j-th
@@ -1332,7 +1559,7 @@ int tune(rafiki_ensemble_s* e, int n, const void* in, hipStream_t s) {
   e->trace.on = false;
   for (size_t mi = 0; mi < NM && rc == RAFIKI_OK; ++mi) {
     const Model& M = e->models[mi];
-    best[mi].assign(M.ops.size(), std::vector<float>(kNumMfmaConfigs + 1, 1e30f));
+    best[mi].assign(M.ops.size(), std::vector<float>(kCfgReduce + 1, 1e30f));
     std::vector<int> out_to_op(M.tensors.size(), -1);
     size_t J = 0;
     for (size_t oi = 0; oi < M.ops.size(); ++oi) {
@@ -1361,7 +1588,7 @@ int tune(rafiki_ensemble_s* e, int n, const void* in, hipStream_t s) {
             break;
           }
           const int oi = r.layer >= 0 && r.layer < (int)out_to_op.size() ? out_to_op[r.layer] : -1;
-          if (oi >= 0 && r.cfg >= 0 && r.cfg <= kCfgDirect)
+          if (oi >= 0 && r.cfg >= 0 && r.cfg <= kCfgReduce)
             best[mi][oi][r.cfg] = std::min(best[mi][oi][r.cfg], ms);
         }
       }
@@ -1402,6 +1629,13 @@ int tune(rafiki_ensemble_s* e, int n, const void* in, hipStream_t s) {
   e->tuned_lean_gemm[n] = std::move(lean_gemm);
   e->tuned_lean[n] = std::move(lean);
   e->tuned[n] = std::move(choice);
+  rc = tune_blocks(e, n, in, s, best, est);
+  if (rc) {
+    e->tuned_lean_gemm.erase(n);
+    e->tuned_lean.erase(n);
+    e->tuned.erase(n);
+    return rc;
+  }
   e->model_ms[n] = std::move(est);
   return RAFIKI_OK;
 }
@@ -1576,7 +1810,17 @@ int run_models(const rafiki_ensemble_s* e, const int* mis, int nm, const void* i
                hipStream_t s, size_t op_begin, size_t op_end, const CallScratch* ws) {
   if (nm < 1 || nm > kMaxGroup) return fail(RAFIKI_ERR_INVALID, "internal: group size");
   op_end = std::min(op_end, e->models[mis[0]].ops.size());
+  const auto bit = e->blocks.find(n);
+  const std::vector<int>* bm = nm == 1 && e->force_tile < 0 && bit != e->blocks.end() ? &bit->second[mis[0]] : nullptr;
   for (size_t oi = op_begin; oi < op_end; ++oi) {
+    const Model& M0 = e->models[mis[0]];
+    const int u = bm && !bm->empty() ? M0.unit_of[oi] : -1;
+    if (u >= 0 && (*bm)[u] > 0) {   // the unit's one launch at its first op
+      if (M0.units[u].first != (int)oi) continue;
+      const int rc = run_block(e, mis[0], M0.units[u], n, (*bm)[u], s);
+      if (rc) return rc;
+      continue;
+    }
     int ois[kMaxGroup];
     for (int k = 0; k < nm; ++k) ois[k] = (int)oi;
     const int rc = run_op(e, mis, ois, nm, in, n, logits, s, ws);
@@ -1755,6 +1999,7 @@ int rafiki_ensemble_create(const rafiki_model_desc* models, int n_models, const 
   if (const char* t = std::getenv("RAFIKI_LEAN_TILES")) e->lean_policy = std::atoi(t) != 0;
   if (const char* t = std::getenv("RAFIKI_GROUPED")) e->grouped = std::atoi(t) != 0;
   if (const char* t = std::getenv("RAFIKI_FUSED_NET")) e->fused_net = std::atoi(t) != 0;
+  if (const char* t = std::getenv("RAFIKI_FUSED_BLOCKS")) e->fused_blocks = std::atoi(t);
   // Pass 1: validate every model and infer shapes without touching the device.
   e->dry = true;
   e->models.resize(n_models);
@@ -2357,7 +2602,7 @@ int rafiki_ensemble_trace_read(rafiki_ensemble_t h, rafiki_trace_rec* out, int c
     st = hipEventElapsedTime(&ms, r.a, r.b);
     if (st != hipSuccess) return fail(RAFIKI_ERR_HIP, std::string("hipEventElapsedTime: ") + hipGetErrorString(st));
     out[i].kind = r.kind; out[i].model = r.model; out[i].layer = r.layer;
-    out[i].flops = r.flops; out[i].bytes = r.bytes; out[i].ms = ms;
+    out[i].flops = r.flops; out[i].bytes = r.bytes; out[i].ms = ms * r.share;
     out[i].tile_cfg = r.tile_cfg; out[i].splits = r.splits;
   }
   h->trace.recs.clear();
