@@ -130,7 +130,11 @@ typedef struct {
  * read one sequence and whose outputs are joined only by concatenations (the TextCNN's
  * kernel widths) are packed as one GEMM whose max over time writes the concatenated
  * vector; every output value is that of its own layer's sum of products (environment
- * RAFIKI_FUSE_BRANCHES=0 at create keeps them apart).
+ * RAFIKI_FUSE_BRANCHES=0 at create keeps them apart).  Where such layers alone read an
+ * embedding of at least 1024 rows and 192 channels, their products are taken once at
+ * create, into an fp32 table [vocab][sum of kw x filters] of at most 4 MiB per request of
+ * max_batch, and a request sums table rows instead (fp32, each tap's sum over the channels
+ * first, then the taps in order).
  * Errors: RAFIKI_ERR_INVALID (null pointers, n_models out of range, mismatched
  * shapes or classes, malformed layers), RAFIKI_ERR_UNSUPPORTED, RAFIKI_ERR_NOMEM,
  * RAFIKI_ERR_HIP.  On error *out is set to NULL. */
@@ -204,7 +208,8 @@ enum {
   RAFIKI_K_CONCAT = 6,         /* vector concatenation */
   RAFIKI_K_COMBINE = 7,        /* softmax + ensemble mean + argmax */
   RAFIKI_K_VOTE = 8,           /* per-model argmax + majority vote */
-  RAFIKI_K_FUSED_NET = 9       /* whole forward pass of small CNNs, one workgroup per image and model */
+  RAFIKI_K_FUSED_NET = 9,      /* whole forward pass of small CNNs, one workgroup per image and model */
+  RAFIKI_K_TAP_TABLE = 10      /* conv1d branches over tokens from their table of per-tap products */
 };
 typedef struct {
   int kind;                     /* RAFIKI_K_* */

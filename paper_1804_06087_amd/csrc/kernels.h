@@ -211,6 +211,28 @@ hipError_t launch_embed_gather(const int32_t* tok, const void* table, void* y, i
 hipError_t launch_concat(const void* a, int ca, int lda, const void* b, int cb, int ldb, void* y, int ldy,
                          int N, int bf16, hipStream_t s);
 
+// Fused conv1d branches over tokens from a table of per-tap products (tap_table.hip): row id
+// of `table` [vocab + 1][ldt] holds, from float first[i] + t * round_up(cnt[i], 4), the
+// products of token id's embedding with tap t of branch i's filters; row vocab is zero and
+// stands for ids outside the table.
+constexpr int kTapThreads = 320;
+constexpr int kTapMaxLen = 8192;    // longest sequence (its row offsets are kept in LDS)
+struct TapArgs {
+  const float* table[kMaxGroup];
+  const float* scale[kMaxGroup];    // folded scale / shift of output row row[i] + c
+  const float* shift[kMaxGroup];
+  bf16_t* y[kMaxGroup];             // concatenated vector [n][ldy] (one part)
+  unsigned* slot[kMaxGroup];        // max keys [n][ldslot] (several parts; launch_maxslot_finish)
+  int n_members;
+  const int32_t* tok;               // [n][len]
+  int len, vocab, ldt, ldy, zero_from, ldslot, relu;
+  int n_branches, quads;            // quads: groups of 4 filters over all branches
+  int kw[kMaxReduceSegs], cnt[kMaxReduceSegs], quad0[kMaxReduceSegs], first[kMaxReduceSegs];
+  int row[kMaxReduceSegs], dst[kMaxReduceSegs];
+  int part_len, segments;           // set by the launch
+};
+hipError_t launch_tap_table(const TapArgs& a, int n, int parts, hipStream_t s);
+
 // Ensemble combine over S selected models' fp32 logits.
 struct CombineArgs {
   const float* logits;  // base of [n_models][ld_model] slots; model m at logits + m * ld_model

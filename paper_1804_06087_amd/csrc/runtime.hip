@@ -90,6 +90,10 @@ struct Op {
   // max keys [max_batch][ldslot], zero between calls
   unsigned* d_slot = nullptr;
   int ldslot = 0;
+  // fused branches over token ids run from a table of per-tap products (tap_table.hip):
+  // rows of ldt floats, or null (the GEMM)
+  float* d_taps = nullptr;
+  int ldt = 0;
   // concat
   int ca = 0, cb = 0;
 };
@@ -641,6 +645,91 @@ int find_blocks(rafiki_ensemble_s* e, const rafiki_model_desc& md, Model& M) {
   return RAFIKI_OK;
 }
 
+// Build the per-tap product table of fused branches `op` (which alone read `embedding`)
+// where the tap-table kernel is the faster path; otherwise the op keeps its GEMM.
+// Measured with 300-dimensional embeddings and 3 x 100 filters of 3, 4 and 5 taps at 512
+// requests of 256 tokens: 88 us per model against 150 us for the GEMM.  The kernel fetches 4
+// bytes per filter, tap and position at 6 to 7 TB/s where the GEMM spends 2 x channels FLOPs
+// at about 600 TFLOP/s, so the two meet near 190 channels.  The table may take at most
+// kTapBytesPerRequest per request the handle serves (a handle for a few requests does not
+// hold 146 MB per model for them), and vocabularies under kTapMinVocab rows, smaller than any
+// text model's, keep the GEMM, whose outputs are bitwise those of the separate branches.
+// A table that does not fit in memory is not an error: the GEMM serves.
+constexpr int kTapMinChannels = 192, kTapMinVocab = 1024;
+constexpr long long kTapBytesPerRequest = 4LL << 20;
+int build_tap_table(rafiki_ensemble_s* e, const rafiki_model_desc& md, Op& op, const BranchGroup& g,
+                    const void* embedding) {
+  int rows = 0, quads = 0, kw_max = 0;
+  for (int b : g.branches) {
+    const rafiki_layer& L = md.layers[b];
+    rows += L.kw * round_up(L.c_out, 4);
+    quads += (L.c_out + 3) / 4;
+    kw_max = std::max(kw_max, (int)L.kw);
+  }
+  const int ldt = round_up(rows, 32);
+  const long long bytes = (long long)(e->vocab + 1) * ldt * 4;
+  if (op.cin_l < kTapMinChannels || e->vocab < kTapMinVocab || bytes > kTapBytesPerRequest * e->max_batch ||
+      bytes >= (1LL << 32) || (long long)e->vocab * op.Cs_in * 2 >= (1LL << 31) || quads > kTapThreads || kw_max > 8 || op.W > kTapMaxLen)
+    return RAFIKI_OK;
+  // the products as a GEMM: embedding rows x (branch, tap, filter) rows
+  const int Kp = round_up(op.Cs_in, 64), Co_pad = round_up(rows, kCoPadBf16);
+  std::vector<uint16_t> w((size_t)Co_pad * Kp, 0);
+  int first = 0;
+  for (int b : g.branches) {
+    const rafiki_layer& L = md.layers[b];
+    for (int c = 0; c < L.c_out; ++c)
+      for (int t = 0; t < L.kw; ++t)
+        for (int ci = 0; ci < L.c_in; ++ci)
+          w[(size_t)(first + t * round_up(L.c_out, 4) + c) * Kp + ci] =
+              host_f2bf(L.weight[((size_t)c * L.c_in + ci) * L.kw + t]);
+    first += L.kw * round_up(L.c_out, 4);
+  }
+  std::vector<float> fold((size_t)2 * Co_pad, 0.f);
+  std::fill(fold.begin(), fold.begin() + Co_pad, 1.f);
+  void *dw = nullptr, *df = nullptr, *dt = nullptr;
+  hipError_t st = hipMalloc(&dt, (size_t)bytes);
+  if (st == hipSuccess) st = hipMalloc(&dw, w.size() * 2);
+  if (st == hipSuccess) st = hipMalloc(&df, fold.size() * 4);
+  unsigned* slot = nullptr;
+  const size_t slot_bytes = (size_t)e->max_batch * round_up(op.c_out, 8) * 4;
+  if (st == hipSuccess && !op.d_slot) st = hipMalloc((void**)&slot, slot_bytes);
+  if (st == hipSuccess) st = hipMemcpy(dw, w.data(), w.size() * 2, hipMemcpyHostToDevice);
+  if (st == hipSuccess) st = hipMemcpy(df, fold.data(), fold.size() * 4, hipMemcpyHostToDevice);
+  if (st == hipSuccess) st = hipMemset(dt, 0, (size_t)bytes);
+  if (st == hipSuccess && slot) st = hipMemset(slot, 0, slot_bytes);
+  if (st == hipSuccess) {
+    ConvArgs a{};
+    a.x = embedding; a.w = dw; a.scale = (const float*)df; a.shift = a.scale + Co_pad; a.y = dt;
+    a.N = a.M = e->vocab; a.H = a.W = a.Ho = a.Wo = a.kh = a.kw = a.stride = 1;
+    a.Cs = a.K = op.Cs_in; a.Kp = Kp; a.Co_pad = Co_pad; a.Nc = rows; a.c_write = rows; a.ldy = ldt; a.out_f32 = 1;
+    a.kt_per_split = Kp / 64;
+    a.x_bytes = (int)((long long)e->vocab * op.Cs_in * 2);
+    a.w_bytes = (int)((long long)Co_pad * Kp * 2);
+    a.Cs8 = op.Cs_in / 8; a.K8 = op.Cs_in / 8;
+    a.mag_cs8 = (unsigned)((((unsigned long long)1 << 32) + a.Cs8 - 1) / a.Cs8);
+    st = launch_conv_mfma(a, default_cfg(rows), 1, nullptr);
+  }
+  if (st == hipSuccess) st = hipStreamSynchronize(nullptr);
+  if (dw) (void)hipFree(dw);
+  if (df) (void)hipFree(df);
+  if (st != hipSuccess) {
+    if (dt) (void)hipFree(dt);
+    if (slot) (void)hipFree(slot);
+    if (st != hipErrorOutOfMemory) return fail(RAFIKI_ERR_HIP, std::string("tap table: ") + hipGetErrorString(st));
+    (void)hipGetLastError();
+    return RAFIKI_OK;
+  }
+  e->allocs.push_back(dt);
+  op.d_taps = (float*)dt;
+  op.ldt = ldt;
+  if (slot) {
+    e->allocs.push_back(slot);
+    op.d_slot = slot;
+    op.ldslot = round_up(op.c_out, 8);
+  }
+  return RAFIKI_OK;
+}
+
 // Validate one model, infer shapes, build its ops and upload its parameters.
 int build_model(rafiki_ensemble_s* e, int mi, const rafiki_model_desc& md, Model& M) {
   if (md.n_layers < 1 || !md.layers) return fail(RAFIKI_ERR_INVALID, "model " + std::to_string(mi) + ": no layers");
@@ -814,7 +903,8 @@ int build_model(rafiki_ensemble_s* e, int mi, const rafiki_model_desc& md, Model
     int rc = fuse_branches(e, md, M, groups);
     if (rc) return rc;
     // A fused GEMM that alone reads an embedding gathers the embedding rows through
-    // the token ids itself: the embedded sequence is never stored.
+    // the token ids itself (or runs from the table of per-tap products): the embedded
+    // sequence is never stored.
     std::vector<int> readers(M.tensors.size(), 0), writer(M.tensors.size(), -1);
     for (size_t i = 0; i < M.ops.size(); ++i) {
       for (int src : {M.ops[i].in, M.ops[i].in2})
@@ -823,11 +913,19 @@ int build_model(rafiki_ensemble_s* e, int mi, const rafiki_model_desc& md, Model
     }
     std::vector<char> drop(M.ops.size(), 0);
     for (Op& op : M.ops) {
-      if (op.nseg == 0 || op.tap_stride == 0 || op.kw > kMaxGatherTaps || op.in < 0 || readers[op.in] != 1) continue;
+      if (op.nseg == 0 || op.in < 0 || readers[op.in] != 1) continue;
       const int wi = writer[op.in];
       if (wi < 0 || M.ops[wi].kind != O_EMBED) continue;
-      if (e->vocab >= 0xFFFF || (long long)e->vocab * op.Cs_in * (long long)e->esz() >= (1LL << 31)) continue;
-      op.table = M.ops[wi].d_w;
+      const bool gathers = op.tap_stride != 0 && op.kw <= kMaxGatherTaps && e->vocab < 0xFFFF &&
+                           (long long)e->vocab * op.Cs_in * (long long)e->esz() < (1LL << 31);
+      if (!e->dry)
+        for (const BranchGroup& g : groups)
+          if (g.root == op.out) {
+            int trc = build_tap_table(e, md, op, g, M.ops[wi].d_w);
+            if (trc) return trc;
+          }
+      if (!gathers && !op.d_taps) continue;
+      if (gathers) op.table = M.ops[wi].d_w;
       op.in = -1;
       drop[wi] = 1;
     }
@@ -903,7 +1001,7 @@ size_t partial_need(const rafiki_ensemble_s* e, const Model& M) {
   if (e->precision != RAFIKI_BF16) return 0;
   size_t need = 0;
   for (const Op& op : M.ops) {
-    if (op.kind != O_CONV && op.kind != O_CONV1D) continue;
+    if ((op.kind != O_CONV && op.kind != O_CONV1D) || op.d_taps) continue;
     for (int n = 1; n <= e->max_batch; ++n) {
       const int Mrows = n * op.Ho * op.Wo;
       const int s = choose_splits(Mrows, op.c_out, op.Kp / 64);
@@ -1318,6 +1416,14 @@ int run_block(const rafiki_ensemble_s* e, int mi, const BlockUnit& u, int n, int
   return RAFIKI_OK;
 }
 
+// Workgroups per request of a tap-table launch of `requests` (over all members): enough to
+// fill the device.  One per request writes the vector itself; several merge their maxima
+// through slots and a second launch.  Measured (us, one launch): 512 requests 94 with 1 or 4;
+// 128: 35 with 1, 27 with 2 to 4; 64: 33, 21, 17, 16 with 1, 2, 4, 8; 3: 30, 16, 10, 7.
+int tap_parts(int requests, int len) {
+  return std::max(1, std::min({16, (512 + requests - 1) / requests, len / 16}));
+}
+
 int run_gemm(const rafiki_ensemble_s* e, const Op& op, ConvArgs a, hipStream_t s, int mi, int li, int cfg,
              const CallScratch* ws = nullptr, const int* mis = nullptr) {
   const int nm = a.n_members > 1 ? a.n_members : 1;   // grouped launch: members mis[0 .. nm)
@@ -1530,7 +1636,7 @@ int tune(rafiki_ensemble_s* e, int n, const void* in, hipStream_t s) {
     cand[mi].resize(M.ops.size());
     for (size_t oi = 0; oi < M.ops.size(); ++oi) {
       const Op& op = M.ops[oi];
-      if (op.kind != O_CONV && op.kind != O_CONV1D) continue;
+      if ((op.kind != O_CONV && op.kind != O_CONV1D) || op.d_taps) continue;
       const int M_rows = n * op.Ho * op.Wo;
       const int splits = choose_splits(M_rows, op.c_out, op.Kp / 64);
       choice[mi][oi] = splits > 1 ? split_cfg(op.c_out) : default_cfg(op.c_out);
@@ -1708,6 +1814,52 @@ int run_op(const rafiki_ensemble_s* e, const int* mis, const int* ois, int nm, c
             g.res = ok.in2 >= 0 ? xptr(k, ok.in2) : nullptr;
           }
         }
+        if (op.d_taps) {
+          TapArgs t{};
+          t.n_members = nm;
+          double vals = 0.0;
+          for (int k = 0; k < nm; ++k) {
+            const Op& ok = mop(k);
+            t.table[k] = ok.d_taps;
+            t.scale[k] = ok.d_scale;
+            t.shift[k] = ok.d_shift;
+            t.y[k] = (bf16_t*)yptr(k);
+            t.slot[k] = slotptr(k);
+          }
+          t.tok = (const int32_t*)in;
+          t.len = op.W; t.vocab = e->vocab; t.ldt = op.ldt; t.ldy = y.Cs; t.zero_from = y.c; t.ldslot = op.ldslot;
+          t.relu = op.relu; t.n_branches = op.nseg;
+          ReduceSegs segs{};
+          segs.n = op.nseg; segs.ldy = y.Cs; segs.zero_from = y.c;
+          int first = 0;
+          for (int i = 0; i < op.nseg; ++i) {
+            t.dst[i] = segs.dst[i] = i ? op.seg_end[i - 1] : 0;
+            t.cnt[i] = segs.cnt[i] = op.seg_end[i] - segs.dst[i];
+            t.row[i] = segs.src[i] = op.seg_row[i];
+            t.kw[i] = op.seg_kw[i];
+            segs.len[i] = op.W - op.seg_kw[i] + 1;
+            t.quad0[i] = t.quads;
+            t.first[i] = first;
+            t.quads += (t.cnt[i] + 3) / 4;
+            first += t.kw[i] * round_up(t.cnt[i], 4);
+            vals += (double)segs.len[i] * t.cnt[i] * t.kw[i];
+          }
+          const int parts = tap_parts(n * nm, op.W);
+          TRACED(e, s, RAFIKI_K_TAP_TABLE, mi, li, 0.0, nm * (double)n * (op.W * 4.0 + vals * 4.0 + y.c * es),
+                 launch_tap_table(t, n, parts, s));
+          if (parts > 1) {
+            GroupIO fin{};
+            fin.n = nm;
+            for (int k = 0; k < nm; ++k) {
+              fin.slot[k] = t.slot[k];
+              fin.y[k] = t.y[k];
+            }
+            TRACED(e, s, RAFIKI_K_POOL, mi, li, 0.0,
+                   nm * ((double)n * op.ldslot * 4.0 * 2.0 + (double)n * y.Cs * es),
+                   launch_maxslot_finish(fin, op.ldslot, n, segs, s));
+          }
+          break;
+        }
         if (op.kind == O_CONV1D) {
           void* tmp = M.d_arena + op.tmp_off;
           a.y = tmp; a.c_write = round_up(op.c_out, 8); a.ldy = a.c_write; a.out_f32 = bf ? 0 : 1;
@@ -1870,10 +2022,10 @@ bool same_structure(const Model& A, const Model& B) {
     const Op &a = A.ops[i], &b = B.ops[i];
     const int fa[] = {a.kind, a.in, a.in2, a.out, a.H, a.W, a.Cs_in, a.Ho, a.Wo, a.kh, a.kw, a.stride, a.pad, a.relu,
                       a.K, a.Kp, a.Co_pad, a.c_out, a.cin_l, a.k, a.pool2, a.nseg, a.tap_stride, a.ldslot, a.ca, a.cb,
-                      a.table != nullptr, a.d_slot != nullptr};
+                      a.table != nullptr, a.d_slot != nullptr, a.d_taps != nullptr};
     const int fb[] = {b.kind, b.in, b.in2, b.out, b.H, b.W, b.Cs_in, b.Ho, b.Wo, b.kh, b.kw, b.stride, b.pad, b.relu,
                       b.K, b.Kp, b.Co_pad, b.c_out, b.cin_l, b.k, b.pool2, b.nseg, b.tap_stride, b.ldslot, b.ca, b.cb,
-                      b.table != nullptr, b.d_slot != nullptr};
+                      b.table != nullptr, b.d_slot != nullptr, b.d_taps != nullptr};
     if (std::memcmp(fa, fb, sizeof(fa)) != 0 || a.tmp_off != b.tmp_off) return false;
     for (int j = 0; j < kMaxReduceSegs; ++j)
       if (a.seg_end[j] != b.seg_end[j] || a.seg_kw[j] != b.seg_kw[j] || a.seg_row[j] != b.seg_row[j]) return false;
@@ -2526,7 +2678,7 @@ int rafiki_ensemble_infer_noalloc(rafiki_ensemble_t h, const void* batch, int n,
     if (!((model_subset_mask >> m) & 1u) || h->precision != RAFIKI_BF16) continue;
     size_t need = 0;
     for (const Op& op : h->models[m].ops) {
-      if (op.kind != O_CONV && op.kind != O_CONV1D) continue;
+      if ((op.kind != O_CONV && op.kind != O_CONV1D) || op.d_taps) continue;
       const int rows = n * op.Ho * op.Wo;
       const int sp = choose_splits(rows, op.c_out, op.Kp / 64);
       if (sp > 1) need = std::max(need, (size_t)sp * rows * op.Co_pad * 4);
