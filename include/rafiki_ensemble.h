@@ -126,7 +126,10 @@ typedef struct {
  * residual, the next block's 1x1 reduction; all with ReLU) may run as one launch, which
  * the tuner times against the layers apart; outputs are bitwise the same (environment
  * RAFIKI_FUSED_BLOCKS at create: 0 always apart, 32 or 64 always fused with that many
- * pixels per workgroup).  Also in bf16, conv1d max-over-time layers that
+ * pixels per workgroup).  Layers of few output rows may run in small tiles whose
+ * workgroups sum their own K splits, timed the same way and bitwise the same
+ * (RAFIKI_SMALL_TILES at create: 0 never, 1 to 4 one tile wherever it applies).  Also in
+ * bf16, conv1d max-over-time layers that
  * read one sequence and whose outputs are joined only by concatenations (the TextCNN's
  * kernel widths) are packed as one GEMM whose max over time writes the concatenated
  * vector; every output value is that of its own layer's sum of products (environment
@@ -224,7 +227,8 @@ typedef struct {
                                    configurations for the direct conv kernel, that plus 1 or
                                    2 for a layer of a fused bottleneck launch of 64 or 32
                                    pixels per workgroup (such a launch has one record per
-                                   layer, its time split by their FLOPs); -1 otherwise */
+                                   layer, its time split by their FLOPs), that plus 4 to 7
+                                   for the small-tile kernel; -1 otherwise */
   int splits;                   /* the same launches: K splits (1 = unsplit); 0 otherwise */
 } rafiki_trace_rec;
 

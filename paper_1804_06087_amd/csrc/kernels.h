@@ -165,6 +165,13 @@ constexpr int kCfgDirect = kNumMfmaConfigs;
 bool conv_direct_fits(const ConvArgs& a);
 hipError_t launch_conv_direct(const ConvArgs& a, hipStream_t s);
 hipError_t launch_splitk_reduce(const ConvArgs& a, int splits, int in_bf16, hipStream_t s);
+// Few output rows (conv_small.hip): small tiles, the K splits on the waves of one workgroup
+// and summed there, in the order and with the epilogue of launch_splitk_reduce (which is not
+// needed; splits = 1: unsplit).  Channel-block K order only.
+constexpr int kNumSmallTiles = 4;
+extern const int kSmallTiles[kNumSmallTiles][2];   // pixels x channels
+bool conv_small_fits(const ConvArgs& a, int tile);
+hipError_t launch_conv_small(const ConvArgs& a, int tile, int splits, hipStream_t s);
 // fp32 direct kernel (CUDA-core style FMA loops; used by the fp32 precision mode).
 hipError_t launch_conv_f32(const ConvArgs& a, hipStream_t s);
 

@@ -65,31 +65,34 @@ __device__ __forceinline__ void store8(void* p, long long off, int bf16, const f
 // ---------------------------------------------------------------- input staging
 // One thread per output pixel and 8-channel group: reads C planes (coalesced along
 // w across threads), writes one 16-byte (bf16) or 32-byte (fp32) NHWC chunk.
-__global__ void stage_images_kernel(const float* __restrict__ x, void* y, int N, int C, int H, int W, int Cs,
-                                    int to_bf16) {
-  const int groups = Cs / 8;
-  const long long HW = (long long)H * W;
-  const long long total = (long long)N * HW * groups;
-  const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;
-  const int g = (int)(idx / (N * HW));            // group-major: neighbouring threads share g
-  const long long pix = idx - (long long)g * N * HW;
-  const long long n = pix / HW, hw = pix - n * HW;
+// One thread per pixel and 8-channel group: x = pixels of one image, y = groups, z = images
+// from n0 on (no index is divided: at one image the launch took 6.6 us, most of it two 64-bit
+// divisions before the first load).
+__global__ void stage_images_kernel(const float* __restrict__ x, void* y, int n0, int C, int HW, int Cs, int to_bf16) {
+  const int hw = blockIdx.x * blockDim.x + threadIdx.x;
+  if (hw >= HW) return;
+  const int g = blockIdx.y;
+  const long long n = n0 + (int)blockIdx.z;
   float v[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     const int c = g * 8 + j;
     v[j] = c < C ? x[(n * C + c) * HW + hw] : 0.f;
   }
-  store8(y, pix * Cs + g * 8, to_bf16, v);
+  store8(y, (n * HW + hw) * Cs + g * 8, to_bf16, v);
 }
 
 hipError_t launch_stage_images(const float* x, void* y, int N, int C, int H, int W, int Cs, int to_bf16,
                                hipStream_t s) {
-  const long long total = (long long)N * H * W * (Cs / 8);
-  launch(stage_images_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), s, x, y, N, C, H,
-                     W, Cs, to_bf16);
-  return hipGetLastError();
+  const int HW = H * W;
+  for (int n0 = 0; n0 < N; n0 += 65535) {   // the grid's limit on z
+    const int n = N - n0 < 65535 ? N - n0 : 65535;
+    launch(stage_images_kernel, dim3((unsigned)((HW + 255) / 256), (unsigned)(Cs / 8), (unsigned)n), dim3(256), s, x, y,
+           n0, C, HW, Cs, to_bf16);
+    const hipError_t st = hipGetLastError();
+    if (st != hipSuccess) return st;
+  }
+  return hipSuccess;
 }
 
 // ---------------------------------------------------------------- max-pool
@@ -311,6 +314,45 @@ __global__ __launch_bounds__(THREADS) void spatial_reduce_kernel(GroupIO io, int
   }
 }
 
+// The bf16 mean over at most 64 positions of at least 64 groups, for the few images of a
+// small batch: the sums of spatial_reduce_kernel in its order (4 slices of positions, each in
+// order, folded in order), but with a thread's positions all in flight and blocks of 16
+// groups.  One image of 7 x 7 x 2048 was four blocks of three dependent rounds of loads
+// (8 to 10 us); latency is all it costs.
+constexpr int kGapSlices = kReduceThreads / 64, kGapDepth = 16;
+__global__ __launch_bounds__(64) void gap_small_kernel(GroupIO io, int HW, int G) {
+  const bf16_t* x = (const bf16_t*)io.x[blockIdx.z];
+  const int gl = threadIdx.x & 15, sl = threadIdx.x >> 4;
+  const int g = blockIdx.y * 16 + gl;
+  const long long n = blockIdx.x;
+  __shared__ float part[64 * 8];
+  uint4 q[kGapDepth];
+#pragma unroll
+  for (int i = 0; i < kGapDepth; ++i) {
+    const int p = sl + i * kGapSlices;
+    if (p < HW && g < G) q[i] = *(const uint4*)(x + ((n * HW + p) * G + g) * 8);
+  }
+  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < kGapDepth; ++i)
+    if (sl + i * kGapSlices < HW && g < G) {
+      const uint32_t w[4] = {q[i].x, q[i].y, q[i].z, q[i].w};
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc[j] += bf2f((w[j >> 1] >> (16 * (j & 1))) & 0xFFFFu);
+    }
+#pragma unroll
+  for (int j = 0; j < 8; ++j) part[threadIdx.x * 8 + j] = acc[j];
+  __syncthreads();
+  if (sl != 0 || g >= G) return;
+#pragma unroll
+  for (int r = 1; r < kGapSlices; ++r)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[j] += part[(r * 16 + gl) * 8 + j];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) acc[j] = acc[j] * (1.0f / (float)HW);
+  store8(io.y[blockIdx.z], (n * G + g) * 8, 1, acc);
+}
+
 // Without branches and with at least 16,384 (image, 8-channel group) pairs: one thread
 // per pair reduces the positions 0 .. HW - 1 in increasing order, eight 16-byte
 // streaming loads in flight (fp32 sums; the order is fixed, so results are
@@ -376,7 +418,9 @@ hipError_t launch_spatial_reduce(const GroupIO& io, int N, int HW, int Cs, int i
   const int G = Cs / 8;
   const int GB = G < 64 ? G : 64;
   const dim3 grid((unsigned)N, (unsigned)((G + GB - 1) / GB), io.n);
-  if (sg.n > 0)
+  if (!segs && bf16 && !is_max && G >= 64 && HW <= kGapSlices * kGapDepth)
+    launch(gap_small_kernel, dim3((unsigned)N, (unsigned)((G + 15) / 16), io.n), dim3(64), s, io, HW, G);
+  else if (sg.n > 0)
     launch(spatial_reduce_kernel<1024>, grid, dim3(1024), s, io, HW, Cs, GB, is_max, bf16, sg);
   else
     launch(spatial_reduce_kernel<kReduceThreads>, grid, dim3(kReduceThreads), s, io, HW, Cs, GB, is_max, bf16, sg);

@@ -211,6 +211,9 @@ struct rafiki_ensemble_s {
   // RAFIKI_FUSED_BLOCKS at create: 0 the layers always apart, 1 the faster when tuning, 32 or
   // 64 always fused with that many pixels per workgroup
   int fused_blocks = 1;
+  // RAFIKI_SMALL_TILES at create: 0 the small-tile kernel never, 1 to kNumSmallTiles that tile
+  // on every layer it takes, unset (-1) the faster when tuning
+  int small_tiles = -1;
   // Per batch size: each model's forward time alone, estimated when tuning (sum of the
   // chosen tiles' times; GEMM FLOPs / 1e12 when tiles are not timed).
   std::map<int, std::vector<double>> model_ms;
@@ -1292,6 +1295,11 @@ int& lean_gemm_model() {
 // Tile ids beyond the GEMM's and the direct kernel's: fused bottleneck launches of 64 and 32
 // pixels per workgroup, and (in the tuner's records only) a split-K reduce launch.
 constexpr int kCfgBlock64 = kCfgDirect + 1, kCfgBlock32 = kCfgDirect + 2, kCfgReduce = kCfgDirect + 3;
+// and the small-tile kernel's tiles (conv_small.hip), candidates of every layer it takes whose
+// launch has at most kSmallMaxRows output rows: beyond, the tiled kernel was the faster for
+// every layer of the image models (it fills the chip with tiles that load fewer bytes).
+constexpr int kCfgSmall = kCfgReduce + 1, kCfgEnd = kCfgSmall + kNumSmallTiles;
+constexpr int kSmallMaxRows = 16384;
 constexpr int kBlockTiles[2] = {64, 32};
 
 // A tile of the lean set: 8 waves, at least 128 x 128, K tiles of 64 (one barrier per 64
@@ -1463,12 +1471,15 @@ int run_gemm(const rafiki_ensemble_s* e, const Op& op, ConvArgs a, hipStream_t s
     splits = (cb + a.kt_per_split - 1) / a.kt_per_split;
   }
   if (cfg == kCfgDirect && (splits > 1 || !conv_direct_fits(a))) cfg = -1;   // e.g. a grouped launch
+  if (cfg >= kCfgSmall && !conv_small_fits(a, cfg - kCfgSmall)) cfg = -1;
   if (cfg < 0) cfg = splits > 1 ? split_cfg(op.c_out) : default_cfg(op.c_out);
   struct TileScope {
     TileScope(int c, int sp) { trace_tile() = {c, sp}; }
     ~TileScope() { trace_tile() = {}; }
   } tile_scope(cfg, splits);
-  if (splits > 1) {
+  if (cfg >= kCfgSmall) {   // sums its splits itself
+    TRACED(e, s, RAFIKI_K_CONV_MFMA, mi, li, flops, bytes, launch_conv_small(a, cfg - kCfgSmall, splits, s));
+  } else if (splits > 1) {
     for (int k = 0; k < nm; ++k) {
       const int m = nm > 1 ? mis[k] : mi;
       const Model& Mo = e->models[m];
@@ -1543,13 +1554,20 @@ inline int run_model(const rafiki_ensemble_s* e, int mi, const void* in, int n, 
   return run_models(e, &mi, 1, in, n, &logits, s, op_begin, op_end, ws);
 }
 
+// Time of op's launches with tile cfg, from the tuner's shortest launches `best`: a split
+// launch of the tiled kernel is followed by its reduce launch.  Each launch beyond the first
+// counts kLaunchGapMs, the time between two dependent launches of a stream beyond their own
+// execution (a chain of empty launches takes 2.6 us each, of which about 1 us is execution).
+constexpr float kLaunchGapMs = 0.0015f;
+float op_time(const Op& op, int n, const std::vector<float>& best, int cfg) {
+  const bool reduce = cfg < kNumMfmaConfigs && choose_splits(n * op.Ho * op.Wo, op.c_out, op.Kp / 64) > 1;
+  return best[cfg] + (reduce ? best[kCfgReduce] + kLaunchGapMs : 0.f);
+}
+
 // Fused or apart, for each block unit at batch size n: the fused launch with 64 and with 32
 // pixels per workgroup, timed like the tiles inside forward passes, against its layers'
-// fastest launches (`best`) with their split-K reduces.  Each launch saved counts
-// kLaunchGapMs, the time between two dependent launches of a stream beyond their own
-// execution (a chain of empty launches takes 2.6 us each, of which about 1 us is execution).
+// fastest launches (`best`) with their split-K reduces, each launch saved counting kLaunchGapMs.
 // Updates the models' estimated times `est`.
-constexpr float kLaunchGapMs = 0.0015f;
 int tune_blocks(rafiki_ensemble_s* e, int n, const void* in, hipStream_t s,
                 const std::vector<std::vector<std::vector<float>>>& best, std::vector<double>& est) {
   const size_t NM = e->models.size();
@@ -1592,10 +1610,9 @@ int tune_blocks(rafiki_ensemble_s* e, int n, const void* in, hipStream_t s,
       float conv = 0.f, apart = -kLaunchGapMs;
       for (int k = M.units[u].first; k <= M.units[u].last; ++k) {
         const Op& op = M.ops[k];
-        const float c = best[mi][k][e->tuned[n][mi][k]];
+        const float c = op_time(op, n, best[mi][k], e->tuned[n][mi][k]);
         conv += c;
         apart += c + kLaunchGapMs;
-        if (choose_splits(n * op.Ho * op.Wo, op.c_out, op.Kp / 64) > 1) apart += best[mi][k][kCfgReduce] + kLaunchGapMs;
       }
       int v = t[u][1] < t[u][0] ? 1 : 0;
       if (e->fused_blocks > 1) v = e->fused_blocks == kBlockTiles[1] ? 1 : 0;
@@ -1645,6 +1662,8 @@ int tune(rafiki_ensemble_s* e, int n, const void* in, hipStream_t s) {
       for (int cfg = 0; cfg < kNumMfmaConfigs; ++cfg)
         if (cfg_fits(cfg, op.c_out) && kMfmaConfigs[cfg].bm <= 2 * round_up(M_rows, 32)) cand[mi][oi].push_back(cfg);
       if (splits == 1 && direct_op_fits(e, M, op)) cand[mi][oi].push_back(kCfgDirect);
+      if (e->small_tiles < 0 && op.kind == O_CONV && op.Cs_in % 64 == 0 && M_rows <= kSmallMaxRows)
+        for (int t = 0; t < kNumSmallTiles; ++t) cand[mi][oi].push_back(kCfgSmall + t);
     }
   }
   if (!timing) {
@@ -1665,7 +1684,7 @@ int tune(rafiki_ensemble_s* e, int n, const void* in, hipStream_t s) {
   e->trace.on = false;
   for (size_t mi = 0; mi < NM && rc == RAFIKI_OK; ++mi) {
     const Model& M = e->models[mi];
-    best[mi].assign(M.ops.size(), std::vector<float>(kCfgReduce + 1, 1e30f));
+    best[mi].assign(M.ops.size(), std::vector<float>(kCfgEnd, 1e30f));
     std::vector<int> out_to_op(M.tensors.size(), -1);
     size_t J = 0;
     for (size_t oi = 0; oi < M.ops.size(); ++oi) {
@@ -1694,7 +1713,7 @@ int tune(rafiki_ensemble_s* e, int n, const void* in, hipStream_t s) {
             break;
           }
           const int oi = r.layer >= 0 && r.layer < (int)out_to_op.size() ? out_to_op[r.layer] : -1;
-          if (oi >= 0 && r.cfg >= 0 && r.cfg <= kCfgReduce)
+          if (oi >= 0 && r.cfg >= 0 && r.cfg < kCfgEnd)
             best[mi][oi][r.cfg] = std::min(best[mi][oi][r.cfg], ms);
         }
       }
@@ -1709,8 +1728,10 @@ int tune(rafiki_ensemble_s* e, int n, const void* in, hipStream_t s) {
     lean[mi] = choice[mi];
     for (size_t oi = 0; oi < cand[mi].size(); ++oi) {
       float t = 1e30f;
-      for (int cfg : cand[mi][oi])
-        if (best[mi][oi][cfg] < t) { t = best[mi][oi][cfg]; choice[mi][oi] = cfg; }
+      for (int cfg : cand[mi][oi]) {
+        const float tc = op_time(e->models[mi].ops[oi], n, best[mi][oi], cfg);
+        if (tc < t) { t = tc; choice[mi][oi] = cfg; }
+      }
       if (t < 1e29f) est[mi] += t;
       const Op& op = e->models[mi].ops[oi];
       lean[mi][oi] = choice[mi][oi];
@@ -1801,6 +1822,8 @@ int run_op(const rafiki_ensemble_s* e, const int* mis, const int* ois, int nm, c
           if (direct_op_fits(e, M, op)) cfg = kCfgDirect;
         } else if (e->force_tile >= 0 && cfg_fits(e->force_tile, op.c_out)) {
           cfg = e->force_tile;
+        } else if (e->small_tiles > 0 && op.kind == O_CONV && bf) {
+          cfg = kCfgSmall + e->small_tiles - 1;
         }
         if (nm > 1) {
           a.n_members = nm;
@@ -2152,6 +2175,7 @@ int rafiki_ensemble_create(const rafiki_model_desc* models, int n_models, const 
   if (const char* t = std::getenv("RAFIKI_GROUPED")) e->grouped = std::atoi(t) != 0;
   if (const char* t = std::getenv("RAFIKI_FUSED_NET")) e->fused_net = std::atoi(t) != 0;
   if (const char* t = std::getenv("RAFIKI_FUSED_BLOCKS")) e->fused_blocks = std::atoi(t);
+  if (const char* t = std::getenv("RAFIKI_SMALL_TILES")) e->small_tiles = std::min(std::atoi(t), kNumSmallTiles);
   // Pass 1: validate every model and infer shapes without touching the device.
   e->dry = true;
   e->models.resize(n_models);
