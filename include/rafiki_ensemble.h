@@ -138,6 +138,10 @@ typedef struct {
  * create, into an fp32 table [vocab][sum of kw x filters] of at most 4 MiB per request of
  * max_batch, and a request sums table rows instead (fp32, each tap's sum over the channels
  * first, then the taps in order).
+ * In fp32, a model's leading stride-1 "same" 1x1 and 3x3 convolutions and 2x2 max-pools run
+ * as one launch that reads the request itself (when every model of the handle starts with
+ * at least two such layers), and the mean over positions with the final FC as another
+ * (environment RAFIKI_CHAINS=0 at create: every layer apart).
  * Errors: RAFIKI_ERR_INVALID (null pointers, n_models out of range, mismatched
  * shapes or classes, malformed layers), RAFIKI_ERR_UNSUPPORTED, RAFIKI_ERR_NOMEM,
  * RAFIKI_ERR_HIP.  On error *out is set to NULL. */

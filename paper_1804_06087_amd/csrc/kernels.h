@@ -240,6 +240,43 @@ struct TapArgs {
 };
 hipError_t launch_tap_table(const TapArgs& a, int n, int parts, hipStream_t s);
 
+// fp32 runs of layers in one launch (chain_f32.hip).  A workgroup computes, for band b of one
+// image, rows band_step[l] b + band_base[l] .. of every layer's input (l = 0: the request) and
+// output into LDS buffers [channel][row][column] (offsets and strides in floats; columns
+// start at the padding the reader needs), the last layer's rows to y [n][Ho][Wo][ldy].
+constexpr int kChainThreads = 512, kChainMaxLayers = 8, kChainLdsBytes = 64 * 1024;
+struct ChainLayer {
+  int k;                           // convolution k x k, stride 1, "same" padding; 0: 2x2 max-pool
+  int C, Cs, Co, Co_pad, relu;     // input channels and their weight rows, output channels, weight row length
+  int C4;                          // groups of 4 input channels (planes C .. 4 C4 - 1 stay zero)
+  int ldc, w_off, fold_off;        // LDS weights [taps][4 C4][ldc], ldc output channels (a multiple of 16), and
+                                   // (scale, shift) pairs [ldc]
+  int rows, Ho, Wo, ldy;           // rows per band; output map; y's row
+  int in_off, in_stride, in_plane, out_off, out_stride, out_plane;
+};
+struct ChainArgs {
+  const float* x;                  // [n][C][H][W]
+  float* y[kMaxGroup];
+  const float* w[kMaxGroup][kChainMaxLayers];
+  const float* scale[kMaxGroup][kChainMaxLayers];
+  const float* shift[kMaxGroup][kChainMaxLayers];
+  int C, H, W, in_rows, in_stride, in_plane, in_col;
+  int n_layers, act_floats, lds_floats;   // activation buffers (first), and all of LDS
+  int band_step[kChainMaxLayers + 1], band_base[kChainMaxLayers + 1];
+  ChainLayer layer[kChainMaxLayers];
+};
+hipError_t launch_chain_f32(const ChainArgs& a, int n, int bands, int members, hipStream_t s);
+// Mean over positions and the final FC, fp32, Cs <= 256 channels.
+struct TailArgs {
+  const float* x[kMaxGroup];       // [n][HW][Cs]
+  float* y[kMaxGroup];             // [n][ldy]
+  const float* w[kMaxGroup];       // [Cs][Co_pad]
+  const float* scale[kMaxGroup];
+  const float* shift[kMaxGroup];
+  int HW, Cs, Co_pad, n_out, ldy, relu;
+};
+hipError_t launch_tail_f32(const TailArgs& a, int n, int members, hipStream_t s);
+
 // Ensemble combine over S selected models' fp32 logits.
 struct CombineArgs {
   const float* logits;  // base of [n_models][ld_model] slots; model m at logits + m * ld_model

@@ -108,11 +108,18 @@ struct BlockUnit {
   float* d_table = nullptr;     // (scale, shift) pairs of the three layers
 };
 
+// fp32 models: the leading ops [0, last] that run as one launch (chain_f32.hip; last -1: none)
+// and the mean + final FC that run as another (gap: the mean's op, -1: none).
+struct Chain {
+  int last = -1, gap = -1;
+};
+
 struct Model {
   std::vector<Op> ops;
   std::vector<Tensor> tensors;
   std::vector<BlockUnit> units;
   std::vector<int> unit_of;       // per op: its unit, or -1
+  Chain chain;
   char* d_arena = nullptr;
   size_t arena_bytes = 0;
   float* d_partial = nullptr;     // split-K partial sums (per model: models may run concurrently)
@@ -211,6 +218,8 @@ struct rafiki_ensemble_s {
   // RAFIKI_FUSED_BLOCKS at create: 0 the layers always apart, 1 the faster when tuning, 32 or
   // 64 always fused with that many pixels per workgroup
   int fused_blocks = 1;
+  bool chains = true;               // fp32 runs of layers in one launch (RAFIKI_CHAINS=0 at create: never)
+  bool raw_input = false;           // every model's chain reads the request itself: no staging
   // RAFIKI_SMALL_TILES at create: 0 the small-tile kernel never, 1 to kNumSmallTiles that tile
   // on every layer it takes, unset (-1) the faster when tuning
   int small_tiles = -1;
@@ -648,6 +657,110 @@ int find_blocks(rafiki_ensemble_s* e, const rafiki_model_desc& md, Model& M) {
   return RAFIKI_OK;
 }
 
+// Geometry of model M's chain in bands of `rows` rows of its last layer's output (pointers are
+// set by run_chain).
+ChainArgs plan_chain(const rafiki_ensemble_s* e, const Model& M, int rows) {
+  ChainArgs a{};
+  const int nl = M.chain.last + 1;
+  a.C = e->C; a.H = e->H; a.W = e->W; a.n_layers = nl;
+  // backwards: the rows of each layer's output that the next layer reads
+  int r[kChainMaxLayers + 1];
+  r[nl] = rows;
+  a.band_step[nl] = rows;
+  for (int l = nl - 1; l >= 0; --l) {
+    const Op& op = M.ops[l];
+    if (op.kind == O_MAXPOOL) {
+      r[l] = 2 * r[l + 1];
+      a.band_step[l] = 2 * a.band_step[l + 1];
+      a.band_base[l] = 2 * a.band_base[l + 1];
+    } else {
+      r[l] = r[l + 1] + 2 * op.pad;
+      a.band_step[l] = a.band_step[l + 1];
+      a.band_base[l] = a.band_base[l + 1] - op.pad;
+    }
+  }
+  // forwards: LDS buffer l is the input of layer l.  A convolution reads four planes and 16
+  // neighbouring pixels at once: planes an odd multiple of 16 words apart use every bank.
+  int off = 0;
+  for (int l = 0; l < nl; ++l) {
+    const Op& op = M.ops[l];
+    const int pad = op.kind == O_MAXPOOL ? 0 : op.pad, stride = op.W + 2 * pad, c4 = (op.cin_l + 3) / 4;
+    const int plane = (r[l] * stride + 15) / 32 * 32 + 16;
+    ChainLayer& L = a.layer[l];
+    L.in_off = off; L.in_stride = stride; L.in_plane = plane;
+    if (l == 0) {
+      a.in_rows = r[0]; a.in_stride = stride; a.in_plane = plane; a.in_col = pad;
+    } else {
+      a.layer[l - 1].out_off = off + pad; a.layer[l - 1].out_stride = stride; a.layer[l - 1].out_plane = plane;
+    }
+    L.rows = r[l + 1]; L.Ho = op.Ho; L.Wo = op.Wo; L.relu = op.relu;
+    L.C = op.cin_l; L.C4 = c4; L.Cs = op.Cs_in;
+    if (op.kind == O_MAXPOOL) {
+      L.k = 0; L.Co = op.cin_l; L.ldy = op.Cs_in;
+    } else {
+      L.k = op.kh; L.Co = op.c_out; L.Co_pad = op.Co_pad; L.ldy = M.tensors[op.out].Cs; L.ldc = round_up(L.ldy, 16);
+    }
+    off += 4 * c4 * plane;
+  }
+  a.act_floats = off;
+  for (int l = 0; l < nl; ++l) {
+    ChainLayer& L = a.layer[l];
+    if (L.k == 0) continue;
+    L.w_off = off;
+    off += L.k * L.k * 4 * L.C4 * L.ldc;
+    L.fold_off = off;
+    off += 2 * L.ldc;
+  }
+  a.lds_floats = off;
+  return a;
+}
+
+// The chain and tail of an fp32 image model: from the request on, stride-1 "same" 1x1 and 3x3
+// convolutions without residual and 2x2 max-pools, each read by the next layer only, as long
+// as one output row's band fits in LDS; then the mean over positions and the final FC.  The
+// chain multiplies padding by weights where conv_f32_kernel skips it, so it takes finite
+// weights only.
+void find_chain(rafiki_ensemble_s* e, const rafiki_model_desc& md, Model& M) {
+  M.chain = Chain{};
+  if (e->precision != RAFIKI_FP32 || e->input_kind != RAFIKI_INPUT_IMAGE_NCHW_F32 || !e->chains) return;
+  std::vector<int> readers(M.tensors.size(), 0);
+  for (const Op& op : M.ops)
+    for (int src : {op.in, op.in2})
+      if (src >= 0) ++readers[src];
+  const int nops = (int)M.ops.size();
+  for (int i = 0; i < nops && i < kChainMaxLayers; ++i) {
+    const Op& op = M.ops[i];
+    if (op.in != (i ? M.ops[i - 1].out : -1) || (i && readers[op.in] != 1)) break;
+    if (op.kind == O_MAXPOOL) {
+      if (op.k != 2 || op.stride != 2 || op.pad != 0) break;
+    } else if (op.kind == O_CONV) {
+      if (op.in2 >= 0 || op.stride != 1 || op.kh != op.kw || (op.kh != 1 && op.kh != 3) || op.pad != op.kh / 2 ||
+          M.tensors[op.out].kind != T_IMG || M.tensors[op.out].is_logits)
+        break;
+      const rafiki_layer& L = md.layers[op.out];
+      bool finite = true;
+      for (size_t k = 0; k < (size_t)op.c_out * op.cin_l * op.kh * op.kw; ++k) finite = finite && std::isfinite(L.weight[k]);
+      if (!finite) break;
+    } else {
+      break;
+    }
+    M.chain.last = i;
+    if (plan_chain(e, M, 1).lds_floats * 4 > kChainLdsBytes) {
+      M.chain.last = i - 1;
+      break;
+    }
+  }
+  for (int i = 1; i < nops; ++i)   // the request has no other reader
+    if (M.ops[i].in < 0) M.chain.last = -1;
+  if (M.chain.last < 1) M.chain.last = -1;   // one layer: nothing to join
+  for (int i = 0; i + 1 < nops; ++i) {
+    const Op &g = M.ops[i], &f = M.ops[i + 1];
+    if (g.kind == O_GAP && f.kind == O_CONV && f.in == g.out && readers[g.out] == 1 && M.tensors[f.out].is_logits &&
+        f.Cs_in == g.Cs_in && g.Cs_in <= 256 && f.kh == 1 && f.H == 1 && f.W == 1 && g.in >= 0)
+      M.chain.gap = i;
+  }
+}
+
 // Build the per-tap product table of fused branches `op` (which alone read `embedding`)
 // where the tap-table kernel is the faster path; otherwise the op keeps its GEMM.
 // Measured with 300-dimensional embeddings and 3 x 100 filters of 3, 4 and 5 taps at 512
@@ -968,6 +1081,7 @@ int build_model(rafiki_ensemble_s* e, int mi, const rafiki_model_desc& md, Model
 
   int brc = find_blocks(e, md, M);
   if (brc) return brc;
+  find_chain(e, md, M);
 
   // Liveness-planned arena for max_batch requests (the logits go to the ensemble's slots);
   // a tensor's last use is the index of the last op that reads it.  A fused block reads its
@@ -1421,6 +1535,61 @@ int run_block(const rafiki_ensemble_s* e, int mi, const BlockUnit& u, int n, int
         else e->trace.recs.push_back({RAFIKI_K_CONV_MFMA, mi, op.out, flops, bytes, ea, eb, cfg, 1, (float)(flops / total)});
       }
   }
+  return RAFIKI_OK;
+}
+
+// The chain of nm models of one structure over n requests in one launch.  Bands of rows give
+// each image several compute units while the launch is small, and keep the buffers within
+// LDS: from whole images, halved until there are 256 workgroups or bands are 4 rows (a third
+// of the first layer's rows are then computed twice).
+int run_chain(const rafiki_ensemble_s* e, const int* mis, int nm, const void* in, int n, hipStream_t s) {
+  const Model& M = e->models[mis[0]];
+  const Op& out = M.ops[M.chain.last];
+  int rows = out.Ho;
+  ChainArgs a = plan_chain(e, M, rows);
+  while (rows > 1 && (a.lds_floats * 4 > kChainLdsBytes ||
+                      (rows > 4 && (long long)n * nm * ((out.Ho + rows - 1) / rows) < 256))) {
+    rows = (rows + 1) / 2;
+    a = plan_chain(e, M, rows);
+  }
+  a.x = (const float*)in;
+  double flops = 0.0, bytes = 4.0 * n * e->C * e->H * e->W + 4.0 * nm * n * out.Ho * out.Wo * a.layer[M.chain.last].ldy;
+  for (int k = 0; k < nm; ++k) {
+    const Model& Mk = e->models[mis[k]];
+    a.y[k] = (float*)(Mk.d_arena + Mk.tensors[out.out].off);
+    for (int l = 0; l <= M.chain.last; ++l) {
+      const Op& op = Mk.ops[l];
+      a.w[k][l] = (const float*)op.d_w;
+      a.scale[k][l] = op.d_scale;
+      a.shift[k][l] = op.d_shift;
+      if (op.kind != O_CONV) continue;
+      const double w = (double)op.c_out * op.kh * op.kw * op.cin_l;
+      flops += 2.0 * n * op.Ho * op.Wo * w;
+      bytes += 4.0 * w;
+    }
+  }
+  TRACED(e, s, RAFIKI_K_CONV_F32, mis[0], out.out, flops, bytes, launch_chain_f32(a, n, (out.Ho + rows - 1) / rows, nm, s));
+  return RAFIKI_OK;
+}
+
+// The mean over positions and the final FC of nm models of one structure in one launch.
+int run_tail(const rafiki_ensemble_s* e, const int* mis, int nm, int n, float* const* logits, hipStream_t s) {
+  const Model& M = e->models[mis[0]];
+  const Op &g = M.ops[M.chain.gap], &f = M.ops[M.chain.gap + 1];
+  TailArgs a{};
+  a.HW = g.H * g.W; a.Cs = g.Cs_in; a.Co_pad = f.Co_pad; a.n_out = f.c_out; a.ldy = f.c_out; a.relu = f.relu;
+  for (int k = 0; k < nm; ++k) {
+    const Model& Mk = e->models[mis[k]];
+    const Op& fk = Mk.ops[M.chain.gap + 1];
+    a.x[k] = (const float*)(Mk.d_arena + Mk.tensors[g.in].off);
+    a.y[k] = logits[k];
+    a.w[k] = (const float*)fk.d_w;
+    a.scale[k] = fk.d_scale;
+    a.shift[k] = fk.d_shift;
+  }
+  const double w = (double)f.c_out * f.cin_l;
+  TRACED(e, s, RAFIKI_K_CONV_F32, mis[0], f.out, 2.0 * nm * n * w, 4.0 * nm * ((double)n * (a.HW * a.Cs + f.c_out) + w),
+         launch_tail_f32(a, n, nm, s));
   return RAFIKI_OK;
 }
 
@@ -1985,10 +2154,25 @@ int run_models(const rafiki_ensemble_s* e, const int* mis, int nm, const void* i
                hipStream_t s, size_t op_begin, size_t op_end, const CallScratch* ws) {
   if (nm < 1 || nm > kMaxGroup) return fail(RAFIKI_ERR_INVALID, "internal: group size");
   op_end = std::min(op_end, e->models[mis[0]].ops.size());
+  const Chain& ch = e->models[mis[0]].chain;   // members of a group have the same
   const auto bit = e->blocks.find(n);
   const std::vector<int>* bm = nm == 1 && e->force_tile < 0 && bit != e->blocks.end() ? &bit->second[mis[0]] : nullptr;
   for (size_t oi = op_begin; oi < op_end; ++oi) {
     const Model& M0 = e->models[mis[0]];
+    // the chain's one launch at its first op, unless another model of the handle needs the
+    // images staged
+    if (e->raw_input && (int)oi <= ch.last) {
+      if (oi > 0) continue;
+      const int rc = run_chain(e, mis, nm, in, n, s);
+      if (rc) return rc;
+      continue;
+    }
+    if (ch.gap >= 0 && (int)oi == ch.gap + 1) continue;
+    if (ch.gap >= 0 && (int)oi == ch.gap) {
+      const int rc = run_tail(e, mis, nm, n, logits, s);
+      if (rc) return rc;
+      continue;
+    }
     const int u = bm && !bm->empty() ? M0.unit_of[oi] : -1;
     if (u >= 0 && (*bm)[u] > 0) {   // the unit's one launch at its first op
       if (M0.units[u].first != (int)oi) continue;
@@ -2012,13 +2196,14 @@ int check_call(const rafiki_ensemble_s* h, const void* batch, int n) {
   return RAFIKI_OK;
 }
 
-// The forward passes' input: the staging buffer for images, the batch itself for tokens.
+// The forward passes' input: the staging buffer for images, the batch itself for tokens and
+// where every model reads the request as it is.
 const void* model_input(const rafiki_ensemble_s* e, const void* batch, void* staged) {
-  return e->input_kind == RAFIKI_INPUT_IMAGE_NCHW_F32 ? staged : batch;
+  return e->input_kind == RAFIKI_INPUT_IMAGE_NCHW_F32 && !e->raw_input ? staged : batch;
 }
 
 int stage(const rafiki_ensemble_s* e, const void* batch, int n, hipStream_t s, void* dst) {
-  if (e->input_kind != RAFIKI_INPUT_IMAGE_NCHW_F32) return RAFIKI_OK;
+  if (e->input_kind != RAFIKI_INPUT_IMAGE_NCHW_F32 || e->raw_input) return RAFIKI_OK;
   TRACED(e, s, RAFIKI_K_STAGE, -1, -1, 0.0, (double)n * e->C * e->H * e->W * (4.0 + (double)e->esz()),
          launch_stage_images((const float*)batch, dst, n, e->C, e->H, e->W, e->in_Cs,
                              e->precision == RAFIKI_BF16, s));
@@ -2033,7 +2218,8 @@ int set_error(int code, const std::string& msg) { return fail(code, msg); }
 // Two models whose layer lists differ only in their parameters: every op and tensor
 // has the same kind, wiring, shapes, padding, tiling fields and arena offsets.
 bool same_structure(const Model& A, const Model& B) {
-  if (A.ops.size() != B.ops.size() || A.tensors.size() != B.tensors.size() || A.arena_bytes != B.arena_bytes)
+  if (A.ops.size() != B.ops.size() || A.tensors.size() != B.tensors.size() || A.arena_bytes != B.arena_bytes ||
+      A.chain.last != B.chain.last || A.chain.gap != B.chain.gap)
     return false;
   for (size_t i = 0; i < A.tensors.size(); ++i) {
     const Tensor &a = A.tensors[i], &b = B.tensors[i];
@@ -2175,6 +2361,7 @@ int rafiki_ensemble_create(const rafiki_model_desc* models, int n_models, const 
   if (const char* t = std::getenv("RAFIKI_GROUPED")) e->grouped = std::atoi(t) != 0;
   if (const char* t = std::getenv("RAFIKI_FUSED_NET")) e->fused_net = std::atoi(t) != 0;
   if (const char* t = std::getenv("RAFIKI_FUSED_BLOCKS")) e->fused_blocks = std::atoi(t);
+  if (const char* t = std::getenv("RAFIKI_CHAINS")) e->chains = std::atoi(t) != 0;
   if (const char* t = std::getenv("RAFIKI_SMALL_TILES")) e->small_tiles = std::min(std::atoi(t), kNumSmallTiles);
   // Pass 1: validate every model and infer shapes without touching the device.
   e->dry = true;
@@ -2209,6 +2396,8 @@ int rafiki_ensemble_create(const rafiki_model_desc* models, int n_models, const 
         break;
       }
   }
+  e->raw_input = e->input_kind == RAFIKI_INPUT_IMAGE_NCHW_F32;
+  for (const Model& M : e->models) e->raw_input = e->raw_input && M.chain.last >= 0;
   // Pairable models: bf16, different layer lists, at least half of the shorter one's
   // ops aligned with ops of the other.
   if (e->precision == RAFIKI_BF16)
@@ -2634,6 +2823,8 @@ static int serve(rafiki_ensemble_t h, const void* batch, int n, uint32_t model_s
     if (rc) return rc;
     if (h->input_kind == RAFIKI_INPUT_TOKENS_I32)
       HIPCHK(hipMemcpyAsync(h->d_tokens, batch, (size_t)n * h->H * 4, hipMemcpyDeviceToDevice, s));
+    else if (h->raw_input)   // the graph reads a buffer of the handle
+      HIPCHK(hipMemcpyAsync(h->d_staged, batch, (size_t)n * h->C * h->H * h->W * 4, hipMemcpyDeviceToDevice, s));
     hipGraphExec_t exec = nullptr;
     rafiki_ensemble_s::Sched sched;
     rc = pick_schedule(h, ca, in, n, model_subset_mask, s, &sched);
