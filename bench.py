@@ -87,9 +87,10 @@ def parse():
     return ap.parse_args()
 
 
-# the bf16 conv launches (trace class conv_mfma): the GEMM kernel and the direct conv kernel
-CONV_SOURCES = [os.path.join(ROOT, "paper_1804_06087_amd", "csrc", f) for f in ("conv_mfma.hip", "conv_direct.hip", "bottleneck.hip")]
-CONV_KERNEL_NAMES = ("conv_mfma_kernel", "conv_direct_kernel", "block_kernel")
+# the bf16 conv launches (trace class conv_mfma)
+CONV_SOURCES = [os.path.join(ROOT, "paper_1804_06087_amd", "csrc", f)
+                for f in ("conv_mfma.hip", "conv_direct.hip", "conv_small.hip", "conv_patch.hip", "bottleneck.hip")]
+CONV_KERNEL_NAMES = ("conv_mfma_kernel", "conv_direct_kernel", "conv_small_kernel", "conv_patch_kernel", "block_kernel")
 
 
 def strip_comments(src: str) -> str:
@@ -649,7 +650,9 @@ def layers_main(args, dev):
             desc = f"{OP_NAMES[L.op]} {L.c_in}->{L.c_out} {L.kh}x{L.kw}/{L.stride}"
             if OP_NAMES[L.op] == "concat" and kind != "concat":   # branches fused into one GEMM + max
                 desc = f"conv1d_maxtime branches -> concat {L.c_out}"
-        special = {n_gemm_cfgs: "direct", n_gemm_cfgs + 1: "block 64", n_gemm_cfgs + 2: "block 32"}
+        names = ["direct", "block 64", "block 32", "", "small 16x16", "small 16x32", "small 32x16", "small 32x32",
+                 "patch flat", "patch x16", "patch x32"]   # the trace's tile ids after the GEMM's
+        special = {n_gemm_cfgs + i: name + (f" / {a['splits']}" if a["splits"] > 1 else "") for i, name in enumerate(names)}
         tile = special.get(a["cfg"], f"{a['cfg']} / {a['splits']}") if a["cfg"] >= 0 else ""
         print(f"| {specs[m].name if m >= 0 else '-'} | {li} | {desc} | {kind} | {tile} | {a['ms'] * 1e3:.1f} | "
               f"{a['flops'] / a['ms'] / 1e9:.0f} | {a['bytes'] / a['ms'] / 1e6:.0f} | {bound} | {tb * 1e3:.1f} | "

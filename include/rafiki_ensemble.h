@@ -128,7 +128,9 @@ typedef struct {
  * RAFIKI_FUSED_BLOCKS at create: 0 always apart, 32 or 64 always fused with that many
  * pixels per workgroup).  Layers of few output rows may run in small tiles whose
  * workgroups sum their own K splits, timed the same way and bitwise the same
- * (RAFIKI_SMALL_TILES at create: 0 never, 1 to 4 one tile wherever it applies).  Also in
+ * (RAFIKI_SMALL_TILES at create: 0 never, 1 to 4 one tile wherever it applies), and 3x3
+ * layers of many channels from an input patch and streamed weights (RAFIKI_PATCH_TILES: 0
+ * never, 1 to 3 one tile wherever it applies).  Also in
  * bf16, conv1d max-over-time layers that
  * read one sequence and whose outputs are joined only by concatenations (the TextCNN's
  * kernel widths) are packed as one GEMM whose max over time writes the concatenated
@@ -232,7 +234,8 @@ typedef struct {
                                    2 for a layer of a fused bottleneck launch of 64 or 32
                                    pixels per workgroup (such a launch has one record per
                                    layer, its time split by their FLOPs), that plus 4 to 7
-                                   for the small-tile kernel; -1 otherwise */
+                                   for the small-tile kernel, plus 8 to 10 for the patch
+                                   kernel; -1 otherwise */
   int splits;                   /* the same launches: K splits (1 = unsplit); 0 otherwise */
 } rafiki_trace_rec;
 

@@ -329,6 +329,16 @@ struct FusedNetArgs {
 };
 hipError_t launch_fused_net(const FusedNetArgs& a, int n, int n_models, hipStream_t s);
 
+// 3x3 stride-1 convolution of 64 q input and 128 p output channels from an LDS patch
+// (conv_patch.hip): cfg 0 consecutive pixels, 1 and 2 rectangles 16 and 32 pixels wide.  w: the
+// weights in its order (launch_pack_patch_weights).  Bitwise the unsplit GEMM.
+constexpr int kNumPatchTiles = 3;
+extern const int kPatchModes[kNumPatchTiles];
+constexpr int kPatchFlatRows = 256;   // patch rows of cfg 0: 128 pixels and a map row and a pixel on either side
+bool conv_patch_fits(const ConvArgs& a, int cfg);
+hipError_t launch_pack_patch_weights(const bf16_t* w, int kp, int co, int K, bf16_t* out, hipStream_t s);
+hipError_t launch_conv_patch(const ConvArgs& a, const void* w, int cfg, hipStream_t s);
+
 // Fused bottleneck block (bottleneck.hip): over M pixels of H x W maps, MID channels,
 //   [3x3 stride 1 pad 1, MID -> MID, ReLU;] 1x1 MID -> 4 MID + residual, ReLU -> y;
 //   [1x1 4 MID -> MID, ReLU -> z], all bf16 NHWC with folded scale / shift.

@@ -73,6 +73,8 @@ struct Op {
   float* d_shift = nullptr;
   // pooling
   int k = 1;
+  // conv2d: the weights once more in conv_patch.hip's order, for the layers it takes
+  void* d_wp = nullptr;
   // conv2d: a 2x2 stride-2 max-pool fused into the epilogue; `out` is the pooled tensor
   int pool2 = 0;
   // conv1d: pre-max scratch [n][T][Cs_out] in the arena
@@ -223,6 +225,7 @@ struct rafiki_ensemble_s {
   // RAFIKI_SMALL_TILES at create: 0 the small-tile kernel never, 1 to kNumSmallTiles that tile
   // on every layer it takes, unset (-1) the faster when tuning
   int small_tiles = -1;
+  int patch_tiles = -1;             // RAFIKI_PATCH_TILES: the same for the patch kernel's tiles
   // Per batch size: each model's forward time alone, estimated when tuning (sum of the
   // chosen tiles' times; GEMM FLOPs / 1e12 when tiles are not timed).
   std::map<int, std::vector<double>> model_ms;
@@ -657,6 +660,27 @@ int find_blocks(rafiki_ensemble_s* e, const rafiki_model_desc& md, Model& M) {
   return RAFIKI_OK;
 }
 
+// Packs the weights of the layers that the patch kernel takes in its order (bf16 3x3 stride-1
+// convolutions without residual over 64 q channels to 128 p) unless the handle is in its
+// validation pass.
+int pack_patches(rafiki_ensemble_s* e, Model& M) {
+  if (e->precision != RAFIKI_BF16 || e->dry || e->patch_tiles == 0) return RAFIKI_OK;
+  bool any = false;
+  for (Op& op : M.ops) {
+    if (op.kind != O_CONV || op.in2 >= 0 || op.in < 0 || op.kh != 3 || op.kw != 3 || op.stride != 1 || op.pad != 1 ||
+        op.Cs_in % 64 != 0 || op.c_out % 128 != 0 || op.Kp != op.K || M.tensors[op.out].kind != T_IMG ||
+        M.tensors[op.out].Cs != op.c_out)
+      continue;
+    int rc = dev_alloc(e, &op.d_wp, (size_t)op.c_out * op.K * 2);
+    if (rc) return rc;
+    const hipError_t st = launch_pack_patch_weights((const bf16_t*)op.d_w, op.Kp, op.c_out, op.K, (bf16_t*)op.d_wp, nullptr);
+    if (st != hipSuccess) return fail(RAFIKI_ERR_HIP, std::string("packing patch weights: ") + hipGetErrorString(st));
+    any = true;
+  }
+  const hipError_t st = any ? hipStreamSynchronize(nullptr) : hipSuccess;
+  return st == hipSuccess ? RAFIKI_OK : fail(RAFIKI_ERR_HIP, std::string("packing patch weights: ") + hipGetErrorString(st));
+}
+
 // Geometry of model M's chain in bands of `rows` rows of its last layer's output (pointers are
 // set by run_chain).
 ChainArgs plan_chain(const rafiki_ensemble_s* e, const Model& M, int rows) {
@@ -1080,6 +1104,7 @@ int build_model(rafiki_ensemble_s* e, int mi, const rafiki_model_desc& md, Model
   }
 
   int brc = find_blocks(e, md, M);
+  if (!brc) brc = pack_patches(e, M);
   if (brc) return brc;
   find_chain(e, md, M);
 
@@ -1412,7 +1437,8 @@ constexpr int kCfgBlock64 = kCfgDirect + 1, kCfgBlock32 = kCfgDirect + 2, kCfgRe
 // and the small-tile kernel's tiles (conv_small.hip), candidates of every layer it takes whose
 // launch has at most kSmallMaxRows output rows: beyond, the tiled kernel was the faster for
 // every layer of the image models (it fills the chip with tiles that load fewer bytes).
-constexpr int kCfgSmall = kCfgReduce + 1, kCfgEnd = kCfgSmall + kNumSmallTiles;
+// After them the patch kernel's tiles (conv_patch.hip), candidates of every unsplit layer it takes.
+constexpr int kCfgSmall = kCfgReduce + 1, kCfgPatch = kCfgSmall + kNumSmallTiles, kCfgEnd = kCfgPatch + kNumPatchTiles;
 constexpr int kSmallMaxRows = 16384;
 constexpr int kBlockTiles[2] = {64, 32};
 
@@ -1640,13 +1666,16 @@ int run_gemm(const rafiki_ensemble_s* e, const Op& op, ConvArgs a, hipStream_t s
     splits = (cb + a.kt_per_split - 1) / a.kt_per_split;
   }
   if (cfg == kCfgDirect && (splits > 1 || !conv_direct_fits(a))) cfg = -1;   // e.g. a grouped launch
-  if (cfg >= kCfgSmall && !conv_small_fits(a, cfg - kCfgSmall)) cfg = -1;
+  if (cfg >= kCfgSmall && cfg < kCfgPatch && !conv_small_fits(a, cfg - kCfgSmall)) cfg = -1;
+  if (cfg >= kCfgPatch && (splits > 1 || !op.d_wp || !conv_patch_fits(a, cfg - kCfgPatch))) cfg = -1;
   if (cfg < 0) cfg = splits > 1 ? split_cfg(op.c_out) : default_cfg(op.c_out);
   struct TileScope {
     TileScope(int c, int sp) { trace_tile() = {c, sp}; }
     ~TileScope() { trace_tile() = {}; }
   } tile_scope(cfg, splits);
-  if (cfg >= kCfgSmall) {   // sums its splits itself
+  if (cfg >= kCfgPatch) {
+    TRACED(e, s, RAFIKI_K_CONV_MFMA, mi, li, flops, bytes, launch_conv_patch(a, op.d_wp, cfg - kCfgPatch, s));
+  } else if (cfg >= kCfgSmall) {   // sums its splits itself
     TRACED(e, s, RAFIKI_K_CONV_MFMA, mi, li, flops, bytes, launch_conv_small(a, cfg - kCfgSmall, splits, s));
   } else if (splits > 1) {
     for (int k = 0; k < nm; ++k) {
@@ -1831,6 +1860,12 @@ int tune(rafiki_ensemble_s* e, int n, const void* in, hipStream_t s) {
       for (int cfg = 0; cfg < kNumMfmaConfigs; ++cfg)
         if (cfg_fits(cfg, op.c_out) && kMfmaConfigs[cfg].bm <= 2 * round_up(M_rows, 32)) cand[mi][oi].push_back(cfg);
       if (splits == 1 && direct_op_fits(e, M, op)) cand[mi][oi].push_back(kCfgDirect);
+      if (splits == 1 && op.d_wp && e->patch_tiles < 0) {
+        ConvArgs a = gemm_args(e, M, op, n, in);
+        a.c_write = a.ldy = op.c_out;
+        for (int t = 0; t < kNumPatchTiles; ++t)
+          if (conv_patch_fits(a, t)) cand[mi][oi].push_back(kCfgPatch + t);
+      }
       if (e->small_tiles < 0 && op.kind == O_CONV && op.Cs_in % 64 == 0 && M_rows <= kSmallMaxRows)
         for (int t = 0; t < kNumSmallTiles; ++t) cand[mi][oi].push_back(kCfgSmall + t);
     }
@@ -1991,6 +2026,8 @@ int run_op(const rafiki_ensemble_s* e, const int* mis, const int* ois, int nm, c
           if (direct_op_fits(e, M, op)) cfg = kCfgDirect;
         } else if (e->force_tile >= 0 && cfg_fits(e->force_tile, op.c_out)) {
           cfg = e->force_tile;
+        } else if (e->patch_tiles > 0 && op.d_wp) {
+          cfg = kCfgPatch + e->patch_tiles - 1;
         } else if (e->small_tiles > 0 && op.kind == O_CONV && bf) {
           cfg = kCfgSmall + e->small_tiles - 1;
         }
@@ -2362,6 +2399,7 @@ int rafiki_ensemble_create(const rafiki_model_desc* models, int n_models, const 
   if (const char* t = std::getenv("RAFIKI_FUSED_NET")) e->fused_net = std::atoi(t) != 0;
   if (const char* t = std::getenv("RAFIKI_FUSED_BLOCKS")) e->fused_blocks = std::atoi(t);
   if (const char* t = std::getenv("RAFIKI_CHAINS")) e->chains = std::atoi(t) != 0;
+  if (const char* t = std::getenv("RAFIKI_PATCH_TILES")) e->patch_tiles = std::min(std::atoi(t), kNumPatchTiles);
   if (const char* t = std::getenv("RAFIKI_SMALL_TILES")) e->small_tiles = std::min(std::atoi(t), kNumSmallTiles);
   // Pass 1: validate every model and infer shapes without touching the device.
   e->dry = true;
