@@ -1435,8 +1435,9 @@ int& lean_gemm_model() {
 // pixels per workgroup, and (in the tuner's records only) a split-K reduce launch.
 constexpr int kCfgBlock64 = kCfgDirect + 1, kCfgBlock32 = kCfgDirect + 2, kCfgReduce = kCfgDirect + 3;
 // and the small-tile kernel's tiles (conv_small.hip), candidates of every layer it takes whose
-// launch has at most kSmallMaxRows output rows: beyond, the tiled kernel was the faster for
-// every layer of the image models (it fills the chip with tiles that load fewer bytes).
+// launch has at most kSmallMaxRows output rows. The bound only keeps the tuner's list short: at
+// 3,136 and 12,544 rows (64 images of ResNet-50 and -101) every convolution already picks a
+// larger tile, which loads fewer bytes per output; the FCs (64 rows) pick 16x16.
 // After them the patch kernel's tiles (conv_patch.hip), candidates of every unsplit layer it takes.
 constexpr int kCfgSmall = kCfgReduce + 1, kCfgPatch = kCfgSmall + kNumSmallTiles, kCfgEnd = kCfgPatch + kNumPatchTiles;
 constexpr int kSmallMaxRows = 16384;

@@ -4,7 +4,7 @@ RAFIKI_SMALL_TILES=1..4 runs every layer the kernel takes with one of its tiles,
 probe ends in a global average pool and a random FC (itself one of the layers): equal logits
 mean equal outputs.  Cases: K split over the waves in one round and in several, unsplit,
 1 x 1 and 3 x 3, strides, residual, the fused 2x2 max-pool, ragged rows and channels, padded
-storage channels, a single row, a grouped launch and a paired lane's two-member launch shape.
+storage channels, a single row, and a grouped launch.
 """
 import numpy as np
 import pytest
