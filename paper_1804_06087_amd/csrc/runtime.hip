@@ -11,6 +11,7 @@
 //   new batch size also times every GEMM op's tile candidates inside forward passes.
 #include "rafiki_ensemble.h"
 #include "kernels.h"
+#include "arena.h"
 #include "greedy.h"
 
 #include <algorithm>
@@ -54,7 +55,7 @@ struct Tensor {
   int kind = T_IMG;
   int c = 0, h = 1, w = 1, Cs = 0;   // logical channels, spatial size, storage channels
   size_t off = 0;                    // byte offset in the model arena
-  int last_use = -1;
+  int last_use = -1;                 // index of the last op that reads it
   bool is_logits = false;
   size_t item_elems() const { return (size_t)h * w * Cs; }
 };
@@ -131,38 +132,6 @@ struct Model {
   void* d_staged_own = nullptr;   // the model's own staged input (asynchronous serving)
   // Whole-network program (fused_net.hip) when every layer fits that kernel; empty if not.
   std::vector<FusedLayer> fprog;
-};
-
-struct FreeList {
-  struct B { size_t off, size; };
-  std::vector<B> free;
-  size_t top = 0;
-  size_t alloc(size_t n) {
-    n = round_up_sz(std::max<size_t>(n, 1), 256);
-    for (size_t i = 0; i < free.size(); ++i) {
-      if (free[i].size >= n) {
-        size_t off = free[i].off;
-        free[i].off += n;
-        free[i].size -= n;
-        if (free[i].size == 0) free.erase(free.begin() + i);
-        return off;
-      }
-    }
-    size_t off = top;
-    top += n;
-    return off;
-  }
-  void release(size_t off, size_t n) {
-    n = round_up_sz(std::max<size_t>(n, 1), 256);
-    free.push_back({off, n});
-    std::sort(free.begin(), free.end(), [](const B& a, const B& b) { return a.off < b.off; });
-    std::vector<B> merged;
-    for (auto& b : free) {
-      if (!merged.empty() && merged.back().off + merged.back().size == b.off) merged.back().size += b.size;
-      else merged.push_back(b);
-    }
-    free.swap(merged);
-  }
 };
 
 }  // namespace
@@ -1108,33 +1077,29 @@ int build_model(rafiki_ensemble_s* e, int mi, const rafiki_model_desc& md, Model
   if (brc) return brc;
   find_chain(e, md, M);
 
-  // Liveness-planned arena for max_batch requests (the logits go to the ensemble's slots);
-  // a tensor's last use is the index of the last op that reads it.  A fused block reads its
-  // inputs while it writes every one of its outputs, so its inputs live to its last op.
-  for (size_t i = 0; i < M.ops.size(); ++i)
-    for (int src : {M.ops[i].in, M.ops[i].in2})
-      if (src >= 0) {
-        const int u = M.unit_of[i];
-        M.tensors[src].last_use = std::max(M.tensors[src].last_use, u >= 0 ? M.units[u].last : (int)i);
-      }
-  FreeList fl;
+  // Liveness-planned arena for max_batch requests (the logits go to the ensemble's slots).
   const size_t es = e->esz(), nb = (size_t)e->max_batch;
+  std::vector<ArenaStep> steps(M.ops.size());
   for (size_t i = 0; i < M.ops.size(); ++i) {
-    Op& op = M.ops[i];
-    Tensor& y = M.tensors[op.out];
-    size_t tmp_bytes = 0;
-    if (op.kind == O_CONV1D) {
-      tmp_bytes = nb * op.Wo * round_up(op.c_out, 8) * es;
-      op.tmp_off = fl.alloc(tmp_bytes);
+    const Op& op = M.ops[i];
+    const Tensor& y = M.tensors[op.out];
+    ArenaStep& st = steps[i];
+    for (int k = 0; k < 2; ++k) {
+      const int src = k ? op.in2 : op.in;
+      st.in[k] = src;
+      if (src >= 0) M.tensors[src].last_use = std::max(M.tensors[src].last_use, (int)i);
     }
-    if (!y.is_logits) y.off = fl.alloc(nb * y.item_elems() * es);
-    if (op.kind == O_CONV1D) fl.release(op.tmp_off, tmp_bytes);
-    for (int src : {op.in, op.in2}) {
-      if (src >= 0 && M.tensors[src].last_use == (int)i && !M.tensors[src].is_logits)
-        fl.release(M.tensors[src].off, nb * M.tensors[src].item_elems() * es);
-    }
+    st.out = op.out;
+    if (!y.is_logits) st.out_bytes = nb * y.item_elems() * es;
+    if (op.kind == O_CONV1D) st.scratch_bytes = nb * op.Wo * round_up(op.c_out, 8) * es;
+    st.last = M.unit_of[i] >= 0 ? M.units[M.unit_of[i]].last : (int)i;
   }
-  M.arena_bytes = std::max<size_t>(fl.top, 256);
+  const ArenaPlan plan = plan_arena(steps, (int)M.tensors.size());
+  for (size_t i = 0; i < M.ops.size(); ++i) {
+    M.ops[i].tmp_off = plan.scratch[i];
+    if (!M.tensors[M.ops[i].out].is_logits) M.tensors[M.ops[i].out].off = plan.off[M.ops[i].out];
+  }
+  M.arena_bytes = std::max<size_t>(plan.bytes, 256);
   return dev_alloc(e, (void**)&M.d_arena, M.arena_bytes);
 }
 
