@@ -142,7 +142,7 @@ typedef struct {
  * first, then the taps in order).
  * In fp32, a model's leading stride-1 "same" 1x1 and 3x3 convolutions and 2x2 max-pools run
  * as one launch that reads the request itself (when every model of the handle starts with
- * at least two such layers), and the mean over positions with the final FC as another
+ * at least two such layers; as many of them as pay at the call's n), and the mean over positions with the final FC as another
  * (environment RAFIKI_CHAINS=0 at create: every layer apart).
  * Errors: RAFIKI_ERR_INVALID (null pointers, n_models out of range, mismatched
  * shapes or classes, malformed layers), RAFIKI_ERR_UNSUPPORTED, RAFIKI_ERR_NOMEM,

@@ -111,8 +111,9 @@ struct BlockUnit {
   float* d_table = nullptr;     // (scale, shift) pairs of the three layers
 };
 
-// fp32 models: the leading ops [0, last] that run as one launch (chain_f32.hip; last -1: none)
-// and the mean + final FC that run as another (gap: the mean's op, -1: none).
+// fp32 models: the leading ops [0, last] that may run as one launch (chain_f32.hip; last -1:
+// none; a batch size may take fewer, chain_ops) and the mean + final FC that run as another
+// (gap: the mean's op, -1: none).
 struct Chain {
   int last = -1, gap = -1;
 };
@@ -191,6 +192,8 @@ struct rafiki_ensemble_s {
   int fused_blocks = 1;
   bool chains = true;               // fp32 runs of layers in one launch (RAFIKI_CHAINS=0 at create: never)
   bool raw_input = false;           // every model's chain reads the request itself: no staging
+  std::map<int, std::vector<int>> chain_last;   // per requests of a launch (batch size times
+                                                // members) and model: last op of its chain
   // RAFIKI_SMALL_TILES at create: 0 the small-tile kernel never, 1 to kNumSmallTiles that tile
   // on every layer it takes, unset (-1) the faster when tuning
   int small_tiles = -1;
@@ -650,11 +653,11 @@ int pack_patches(rafiki_ensemble_s* e, Model& M) {
   return st == hipSuccess ? RAFIKI_OK : fail(RAFIKI_ERR_HIP, std::string("packing patch weights: ") + hipGetErrorString(st));
 }
 
-// Geometry of model M's chain in bands of `rows` rows of its last layer's output (pointers are
-// set by run_chain).
-ChainArgs plan_chain(const rafiki_ensemble_s* e, const Model& M, int rows) {
+// Geometry of model M's chain of ops [0, last] in bands of `rows` rows of its last layer's
+// output (pointers are set by run_chain).
+ChainArgs plan_chain(const rafiki_ensemble_s* e, const Model& M, int last, int rows) {
   ChainArgs a{};
-  const int nl = M.chain.last + 1;
+  const int nl = last + 1;
   a.C = e->C; a.H = e->H; a.W = e->W; a.n_layers = nl;
   // backwards: the rows of each layer's output that the next layer reads
   int r[kChainMaxLayers + 1];
@@ -738,7 +741,7 @@ void find_chain(rafiki_ensemble_s* e, const rafiki_model_desc& md, Model& M) {
       break;
     }
     M.chain.last = i;
-    if (plan_chain(e, M, 1).lds_floats * 4 > kChainLdsBytes) {
+    if (plan_chain(e, M, i, 1).lds_floats * 4 > kChainLdsBytes) {
       M.chain.last = i - 1;
       break;
     }
@@ -1530,26 +1533,75 @@ int run_block(const rafiki_ensemble_s* e, int mi, const BlockUnit& u, int n, int
   return RAFIKI_OK;
 }
 
-// The chain of nm models of one structure over n requests in one launch.  Bands of rows give
+// The chain of ops [0, last] for `requests` requests over all members.  Bands of rows give
 // each image several compute units while the launch is small, and keep the buffers within
 // LDS: from whole images, halved until there are 256 workgroups or bands are 4 rows (a third
 // of the first layer's rows are then computed twice).
-int run_chain(const rafiki_ensemble_s* e, const int* mis, int nm, const void* in, int n, hipStream_t s) {
-  const Model& M = e->models[mis[0]];
-  const Op& out = M.ops[M.chain.last];
-  int rows = out.Ho;
-  ChainArgs a = plan_chain(e, M, rows);
+ChainArgs plan_bands(const rafiki_ensemble_s* e, const Model& M, int last, long long requests, int* bands) {
+  const int Ho = M.ops[last].Ho;
+  int rows = Ho;
+  ChainArgs a = plan_chain(e, M, last, rows);
   while (rows > 1 && (a.lds_floats * 4 > kChainLdsBytes ||
-                      (rows > 4 && (long long)n * nm * ((out.Ho + rows - 1) / rows) < 256))) {
+                      (rows > 4 && requests * ((Ho + rows - 1) / rows) < 256))) {
     rows = (rows + 1) / 2;
-    a = plan_chain(e, M, rows);
+    a = plan_chain(e, M, last, rows);
   }
+  *bands = (Ho + rows - 1) / rows;
+  return a;
+}
+
+// The last op of model M's chain for n requests (over all members): the length whose estimated time, with the
+// ops after it apart, is shortest.  A band recomputes its halo, two rows more for every 3x3
+// below it, so a chain that LDS keeps to bands of a row or two computes each layer several
+// times: six 3x3 layers over 8 channels of a 26 x 20 map took 373 us at 512 images against
+// 239 apart, and four of them with two apart 180; at 8 images all six in one launch, 54 against
+// 76, are the fastest.  The estimates are fitted to chains of 2 to 7 layers over 4 to 24
+// channels at 1 to 512 images, 50 points, where the length they pick is the fastest or within
+// 2 % of it: a workgroup by itself takes 3 us, 1.2 per layer and 0.09 per MFMA of its busiest
+// wave, and a compute unit completes 1.75 workgroups in that time however many its LDS holds; a
+// layer apart takes 4 us and 0.03 per term of K, or its products (storage padding included) at
+// 6 per ps if that is more.  Two layers always join: on maps of 150 to 250 columns that
+// costs up to 5 us at 1 to 8 images (35 against 30) and saves a third from 128 on (78, 116).
+int chain_ops(const rafiki_ensemble_s* e, const Model& M, int n) {
+  auto apart = [&](const Op& op) {
+    const double px = (double)n * op.Ho * op.Wo;
+    if (op.kind == O_MAXPOOL) return std::max(4.0, px * 5 * op.Cs_in * 4 / 4e6);
+    const int K = op.kh * op.kw * op.Cs_in;
+    return std::max(4.0 + 0.03 * K, px * K * M.tensors[op.out].Cs / 6e6);
+  };
+  double best = 1e30, rest = 0.0;
+  int pick = M.chain.last;
+  for (int last = M.chain.last; last >= 1; --last) {
+    int bands = 0;
+    const ChainArgs a = plan_bands(e, M, last, n, &bands);
+    double mfma = 0.0;
+    for (int l = 0; l <= last; ++l) {
+      const ChainLayer& L = a.layer[l];
+      const int tasks = L.k ? (L.rows * L.Wo + 15) / 16 * (L.ldc / 16) : 0, waves = kChainThreads / 64;
+      mfma += (double)((tasks + waves - 1) / waves) * L.k * L.k * L.C4;
+    }
+    const double us = (3.0 + 1.2 * (last + 1) + 0.09 * mfma) * std::max(1.0, (double)n * bands / (256 * 1.75)) + rest;
+    if (us < best) {
+      best = us;
+      pick = last;
+    }
+    rest += apart(M.ops[last]);
+  }
+  return pick;
+}
+
+// The chain of ops [0, last] of nm models of one structure over n requests in one launch.
+int run_chain(const rafiki_ensemble_s* e, const int* mis, int nm, int last, const void* in, int n, hipStream_t s) {
+  const Model& M = e->models[mis[0]];
+  const Op& out = M.ops[last];
+  int bands = 0;
+  ChainArgs a = plan_bands(e, M, last, (long long)n * nm, &bands);
   a.x = (const float*)in;
-  double flops = 0.0, bytes = 4.0 * n * e->C * e->H * e->W + 4.0 * nm * n * out.Ho * out.Wo * a.layer[M.chain.last].ldy;
+  double flops = 0.0, bytes = 4.0 * n * e->C * e->H * e->W + 4.0 * nm * n * out.Ho * out.Wo * a.layer[last].ldy;
   for (int k = 0; k < nm; ++k) {
     const Model& Mk = e->models[mis[k]];
     a.y[k] = (float*)(Mk.d_arena + Mk.tensors[out.out].off);
-    for (int l = 0; l <= M.chain.last; ++l) {
+    for (int l = 0; l <= last; ++l) {
       const Op& op = Mk.ops[l];
       a.w[k][l] = (const float*)op.d_w;
       a.scale[k][l] = op.d_scale;
@@ -1560,7 +1612,7 @@ int run_chain(const rafiki_ensemble_s* e, const int* mis, int nm, const void* in
       bytes += 4.0 * w;
     }
   }
-  TRACED(e, s, RAFIKI_K_CONV_F32, mis[0], out.out, flops, bytes, launch_chain_f32(a, n, (out.Ho + rows - 1) / rows, nm, s));
+  TRACED(e, s, RAFIKI_K_CONV_F32, mis[0], out.out, flops, bytes, launch_chain_f32(a, n, bands, nm, s));
   return RAFIKI_OK;
 }
 
@@ -1805,6 +1857,12 @@ int tune_blocks(rafiki_ensemble_s* e, int n, const void* in, hipStream_t s,
 int tune(rafiki_ensemble_s* e, int n, const void* in, hipStream_t s) {
   if (e->tuned.count(n)) return RAFIKI_OK;
   const size_t NM = e->models.size();
+  if (e->raw_input)
+    for (int k = 1; k <= kMaxGroup; ++k) {
+      std::vector<int> last;
+      for (const Model& M : e->models) last.push_back(chain_ops(e, M, n * k));
+      e->chain_last[n * k] = std::move(last);
+    }
   std::vector<std::vector<int>> choice(NM);
   std::vector<std::vector<std::vector<int>>> cand(NM);
   std::vector<double> est(NM, 0.0);
@@ -2158,15 +2216,17 @@ int run_models(const rafiki_ensemble_s* e, const int* mis, int nm, const void* i
   if (nm < 1 || nm > kMaxGroup) return fail(RAFIKI_ERR_INVALID, "internal: group size");
   op_end = std::min(op_end, e->models[mis[0]].ops.size());
   const Chain& ch = e->models[mis[0]].chain;   // members of a group have the same
+  const auto cit = e->chain_last.find(n * nm);
+  const int chain_last = !e->raw_input ? -1 : cit != e->chain_last.end() ? cit->second[mis[0]] : ch.last;
   const auto bit = e->blocks.find(n);
   const std::vector<int>* bm = nm == 1 && e->force_tile < 0 && bit != e->blocks.end() ? &bit->second[mis[0]] : nullptr;
   for (size_t oi = op_begin; oi < op_end; ++oi) {
     const Model& M0 = e->models[mis[0]];
     // the chain's one launch at its first op, unless another model of the handle needs the
     // images staged
-    if (e->raw_input && (int)oi <= ch.last) {
+    if ((int)oi <= chain_last) {
       if (oi > 0) continue;
-      const int rc = run_chain(e, mis, nm, in, n, s);
+      const int rc = run_chain(e, mis, nm, chain_last, in, n, s);
       if (rc) return rc;
       continue;
     }

@@ -90,8 +90,10 @@ def test_chain_matches_layers(name, n, monkeypatch):
     x = torch.from_numpy(batch).to(DEV)
     z1, p1, k1 = run([spec] * 2, params, x, n, "1", monkeypatch)
     z0, p0, k0 = run([spec] * 2, params, x, n, "0", monkeypatch)
-    # chain, FC, combine, both members at once; "deep" exceeds LDS and leaves a layer apart
-    assert "stage" in k0 and "stage" not in k1 and len(k1) == (4 if name == "deep" else 3)
+    # chain, FC, combine, both members at once; "deep" exceeds LDS and leaves a layer apart, or
+    # more where its bands of one row would recompute too much
+    assert "stage" in k0 and "stage" not in k1
+    assert len(k1) > 4 if (name, n) == ("deep", 70) else len(k1) == (4 if name == "deep" else 3)
     # layers of at most 180 terms (2^-24 each, random signs) and an FC over the whole map
     for a, b in zip(z1, z0):
         assert np.abs(a - b).max() <= 4e-6 * np.abs(b).max()
@@ -131,3 +133,23 @@ def test_mixed_handle_keeps_staging(monkeypatch):
     for spec, p, z in zip((a, b), params, z1):
         ref = oracle.run_model(spec, p, batch)
         assert np.abs(z - ref).max() <= 1e-5 * np.abs(ref).max()
+
+
+def test_deep_chain_shortens_for_large_batches(monkeypatch):
+    """Six 3x3 layers whose bands are one row: all in one launch for few images, where latency
+    counts; for many, where each band's halo is recomputed work, the last layers run apart."""
+    layers = [conv(-1, 3, 8, 3)] + [conv(i, 8, 8, 3) for i in range(5)]
+    spec = model(layers, (3, 26, 20))
+    params = [wl.gen_params(spec, 3, False, "random")]
+    launches = {}
+    for n in (8, 512):
+        x = torch.from_numpy(wl.gen_images(n, (3, 26, 20), "normal", False, seed=n)).to(DEV)
+        z1, p1, k1 = run([spec], params, x, n, "1", monkeypatch)
+        z0, p0, _ = run([spec], params, x, n, "0", monkeypatch)
+        assert "stage" not in k1
+        launches[n] = k1.count("conv_f32")
+        # 72 to 576 terms a layer in fp32, six layers and the mean
+        assert np.abs(z1[0] - z0[0]).max() <= 4e-6 * np.abs(z0[0]).max()
+        assert np.abs(p1 - p0).max() <= 1e-4
+    assert launches[8] == 2                 # the chain, and the mean with the FC
+    assert launches[512] > launches[8]
