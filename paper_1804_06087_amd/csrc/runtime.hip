@@ -654,7 +654,8 @@ int pack_patches(rafiki_ensemble_s* e, Model& M) {
 }
 
 // Geometry of model M's chain of ops [0, last] in bands of `rows` rows of its last layer's
-// output (pointers are set by run_chain).
+// output (pointers are set by run_chain).  Sizes and offsets stop at kChainTooLarge, past LDS.
+constexpr int kChainTooLarge = 1 << 28;
 ChainArgs plan_chain(const rafiki_ensemble_s* e, const Model& M, int last, int rows) {
   ChainArgs a{};
   const int nl = last + 1;
@@ -677,11 +678,12 @@ ChainArgs plan_chain(const rafiki_ensemble_s* e, const Model& M, int last, int r
   }
   // forwards: LDS buffer l is the input of layer l.  A convolution reads four planes and 16
   // neighbouring pixels at once: planes an odd multiple of 16 words apart use every bank.
+  auto capped = [](long long v) { return (int)std::min<long long>(v, kChainTooLarge); };
   int off = 0;
   for (int l = 0; l < nl; ++l) {
     const Op& op = M.ops[l];
     const int pad = op.kind == O_MAXPOOL ? 0 : op.pad, stride = op.W + 2 * pad, c4 = (op.cin_l + 3) / 4;
-    const int plane = (r[l] * stride + 15) / 32 * 32 + 16;
+    const int plane = capped(((long long)r[l] * stride + 15) / 32 * 32 + 16);
     ChainLayer& L = a.layer[l];
     L.in_off = off; L.in_stride = stride; L.in_plane = plane;
     if (l == 0) {
@@ -696,16 +698,16 @@ ChainArgs plan_chain(const rafiki_ensemble_s* e, const Model& M, int last, int r
     } else {
       L.k = op.kh; L.Co = op.c_out; L.Co_pad = op.Co_pad; L.ldy = M.tensors[op.out].Cs; L.ldc = round_up(L.ldy, 16);
     }
-    off += 4 * c4 * plane;
+    off = capped(off + 4LL * c4 * plane);
   }
   a.act_floats = off;
   for (int l = 0; l < nl; ++l) {
     ChainLayer& L = a.layer[l];
     if (L.k == 0) continue;
     L.w_off = off;
-    off += L.k * L.k * 4 * L.C4 * L.ldc;
+    off = capped(off + L.k * L.k * 4LL * L.C4 * L.ldc);
     L.fold_off = off;
-    off += 2 * L.ldc;
+    off = capped(off + 2LL * L.ldc);
   }
   a.lds_floats = off;
   return a;

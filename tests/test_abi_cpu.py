@@ -199,3 +199,24 @@ def test_oversize_max_batch_rejected_at_create():
     if not torch.cuda.is_available():
         rc, _ = _create([s], [_light_params(s)], precision=bd.RAFIKI_BF16, max_batch=333, opts_over=opts)
         assert rc == bd.RAFIKI_ERR_HIP, bd.last_error()
+
+
+def test_fp32_layers_far_beyond_lds():
+    """An fp32 model that may start with a joined run of layers, whose buffers would take more than
+    2^31 bytes of LDS: the run is refused without overflow (this file also runs under the host
+    sanitizers) and the model stays valid."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("a device is present")
+    c = 1 << 25
+    L = [wl.Layer(op=wl.CONV2D, input=-1, c_in=c, c_out=1, kh=1, kw=1, stride=1, pad=0, relu=True, bias=True),
+         wl.Layer(op=wl.CONV2D, input=0, c_in=1, c_out=1, kh=1, kw=1, stride=1, pad=0, relu=True, bias=True),
+         wl.Layer(op=wl.GLOBAL_AVGPOOL, input=1, c_in=1, c_out=1),
+         wl.Layer(op=wl.FC, input=2, c_in=1, c_out=3, bias=True)]
+    spec = wl.ModelSpec("wide", L, 3, (c, 1, 1))
+    params = _light_params(spec)
+    for layer, p in zip(L, params.layers):
+        if layer.has_weight():
+            p.weight = np.zeros(layer.weight_shape(), np.float32)
+    rc, _ = _create([spec], [params], max_batch=1, opts_over={"c": c, "h": 1, "w": 1})
+    assert rc == bd.RAFIKI_ERR_HIP, bd.last_error()
