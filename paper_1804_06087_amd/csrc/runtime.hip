@@ -713,6 +713,19 @@ ChainArgs plan_chain(const rafiki_ensemble_s* e, const Model& M, int last, int r
   return a;
 }
 
+// Whether the mean over HW positions of Cs channels and the final FC of `classes` outputs run
+// as one launch (tail_f32_kernel): one workgroup per request sums HW Cs values and then runs
+// the Cs products of each round of 256 outputs in turn, where the launches apart use more of
+// the chip.  The line lies where the two meet at one image (us apart / joined): 16 channels
+// of 64 x 64 and 1000 outputs 29.0 / 21.2, 24 channels of 64 x 64 28.8 / 28.4, 128 of 24 x 24 and
+// 10 outputs 23.2 / 23.4 (97.2 / 87.5 at 256 images); beyond it 96 channels of 32 x 32 25.8 / 30.4,
+// 64 of 128 x 128 114 / 177, 256 of 7 x 7 and 1000 outputs 21.6 / 29.0, 128 of 16 x 16 and 1000
+// 19.4 / 23.1.  Up to 32 channels the mean by itself is slow (26 to 40 us for 8) and the line
+// lies higher.
+bool tail_joins(long long HW, int Cs, int classes) {
+  return Cs <= 256 && HW * Cs + 256LL * Cs * ((classes - 1) / 256) <= (Cs <= 32 ? 147456 : 90112);
+}
+
 // The chain and tail of an fp32 image model: from the request on, stride-1 "same" 1x1 and 3x3
 // convolutions without residual and 2x2 max-pools, each read by the next layer only, as long
 // as one output row's band fits in LDS; then the mean over positions and the final FC.  The
@@ -754,7 +767,8 @@ void find_chain(rafiki_ensemble_s* e, const rafiki_model_desc& md, Model& M) {
   for (int i = 0; i + 1 < nops; ++i) {
     const Op &g = M.ops[i], &f = M.ops[i + 1];
     if (g.kind == O_GAP && f.kind == O_CONV && f.in == g.out && readers[g.out] == 1 && M.tensors[f.out].is_logits &&
-        f.Cs_in == g.Cs_in && g.Cs_in <= 256 && f.kh == 1 && f.H == 1 && f.W == 1 && g.in >= 0)
+        f.Cs_in == g.Cs_in && f.kh == 1 && f.H == 1 && f.W == 1 && g.in >= 0 &&
+        tail_joins((long long)g.H * g.W, g.Cs_in, f.c_out))
       M.chain.gap = i;
   }
 }

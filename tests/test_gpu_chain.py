@@ -153,3 +153,21 @@ def test_deep_chain_shortens_for_large_batches(monkeypatch):
         assert np.abs(p1 - p0).max() <= 1e-4
     assert launches[8] == 2                 # the chain, and the mean with the FC
     assert launches[512] > launches[8]
+
+
+@pytest.mark.parametrize("hw, c, classes, joined", [
+    ((64, 64), 24, 1000, True), ((24, 24), 128, 10, True), ((7, 7), 64, 1000, True),
+    ((32, 32), 96, 10, False), ((7, 7), 128, 1000, False), ((7, 7), 256, 1000, False), ((128, 128), 16, 10, False),
+])
+def test_tail_joins_small_means_only(hw, c, classes, joined, monkeypatch):
+    """The mean and the FC share a launch only where one workgroup per request is not too little
+    for them; either way the logits are those of the layers apart."""
+    spec = model([conv(-1, 3, c, 1)], (3,) + hw, classes=classes)
+    params = [wl.gen_params(spec, 3, False, "random")]
+    x = torch.from_numpy(wl.gen_images(2, (3,) + hw, "uniform", False, seed=1)).to(DEV)
+    z1, _, k1 = run([spec], params, x, 2, "1", monkeypatch)
+    z0, _, k0 = run([spec], params, x, 2, "0", monkeypatch)
+    assert k0 == ["stage", "conv_f32", "pool", "conv_f32", "combine"]
+    assert k1 == (["stage", "conv_f32", "conv_f32", "combine"] if joined else k0)
+    # means of 49 to 16,384 positive values in slices, in fp32
+    assert np.abs(z1[0] - z0[0]).max() <= 4e-6 * np.abs(z0[0]).max()
