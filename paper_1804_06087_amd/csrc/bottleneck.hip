@@ -21,7 +21,8 @@
 //
 // Bits: each output sums its K terms in the order of the layer-by-layer kernels with the
 // same MFMA, including their split-K partial sums (summed in split order), the same
-// epilogue fma(acc, scale, shift) (+ residual), ReLU and one rounding to bf16.
+// epilogue fma(acc, scale, shift) (+ residual), ReLU (NaNs as in those kernels) and one
+// rounding to bf16.
 #include "kernels.h"
 
 namespace rafiki {
@@ -38,6 +39,8 @@ __device__ __forceinline__ uint32_t pack2_b(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_b{a, b}, bf16x2_b));
 }
 __device__ __forceinline__ float relu_b(float v) { return __int_as_float(max(__float_as_int(v), 0)); }
+// A NaN as a negative one, which relu_b makes 0.
+__device__ __forceinline__ float negative_nan(float v) { return v == v ? v : __uint_as_float(0xFFC00000u); }
 
 // Every wave's LDS accesses are done, then all waves pass.
 __device__ __forceinline__ void lds_barrier() {
@@ -118,9 +121,16 @@ __global__ __launch_bounds__(MID * 2, 2) void block_kernel(BlockArgs a) {
   };
 #pragma unroll
   for (int i = 0; i < D; ++i) wload(i);
+  // The reduce launch of a layer whose K is split makes a NaN 0 (fmaxf), the unsplit kernels' ReLU
+  // keeps a positive one.  A NaN of the matrix cores is negative, so a positive one comes from
+  // the layer's scale or shift: turned here, once, relu_b does for both.
+  constexpr int kFirstA = (HASB ? MID : 0) + 4 * MID;
+  const bool split_b = HASB && a.b_per < 9 * MID / 64, split_a = HASA && a.a_per < 4 * MID / 64;
   for (int i = tid; i < TAB; i += NW * 64) {
-    tab[2 * i] = a.table[2 * i];
-    tab[2 * i + 1] = a.table[2 * i + 1];
+    const bool split = i < MID ? split_b : (i >= kFirstA && split_a);
+    const float sc = a.table[2 * i], sh = a.table[2 * i + 1];
+    tab[2 * i] = split ? negative_nan(sc) : sc;
+    tab[2 * i + 1] = split ? negative_nan(sh) : sh;
   }
   if (tid < 8) zero[tid] = make_uint4(0u, 0u, 0u, 0u);
   uint4* const in0 = HASB ? xbuf : mid;

@@ -29,12 +29,28 @@ namespace rafiki {
 namespace {
 typedef __bf16 bf16x8_s __attribute__((ext_vector_type(8)));
 typedef float f32x4_s __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2_s __attribute__((ext_vector_type(2)));
+typedef float f32x2_s __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ float bf2f_s(uint32_t b16) { return __uint_as_float(b16 << 16); }
 __device__ __forceinline__ uint32_t f2bf_s(float f) {   // nearest, ties to even (finite)
   uint32_t u = __float_as_uint(f);
   u += 0x7FFFu + ((u >> 16) & 1u);
   return u >> 16;
+}
+// ReLU and rounding of two values as the launch that the tile stands for takes them: the reduce
+// launch of a split K (fmaxf, which makes a NaN 0), or the unsplit tiled kernel (an integer max,
+// which keeps a positive NaN, and the hardware's rounding).  Alike for every other value.
+__device__ __forceinline__ uint32_t pack2_s(float a, float b, bool relu, bool split) {
+  if (split) {
+    if (relu) { a = fmaxf(a, 0.f); b = fmaxf(b, 0.f); }
+    return f2bf_s(a) | (f2bf_s(b) << 16);
+  }
+  if (relu) {
+    a = __int_as_float(max(__float_as_int(a), 0));
+    b = __int_as_float(max(__float_as_int(b), 0));
+  }
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_s{a, b}, bf16x2_s));
 }
 }  // namespace
 
@@ -53,9 +69,10 @@ __device__ __forceinline__ SmallFold small_fold(const ConvArgs& a, int m, int c)
     f.res = *(const uint2*)((const bf16_t*)a.res + (long long)m * a.ldy + c);
   return f;
 }
-// One lane's 4 channels c .. c + 3 of GEMM row m: the epilogue of the split-K reduction.
+// One lane's 4 channels c .. c + 3 of GEMM row m: the epilogue of the split-K reduction, or
+// (split false) of the unsplit tiled kernel.
 // With the fused 2x2 max-pool the four rows of a window are four neighbouring lanes.
-__device__ __forceinline__ void small_epilogue(const ConvArgs& a, f32x4_s acc, const SmallFold& f, int m, int c) {
+__device__ __forceinline__ void small_epilogue(const ConvArgs& a, f32x4_s acc, const SmallFold& f, int m, int c, bool split) {
   float v[4] = {acc[0] * f.sc.x + f.sh.x, acc[1] * f.sc.y + f.sh.y, acc[2] * f.sc.z + f.sh.z,
                 acc[3] * f.sc.w + f.sh.w};
   if (a.pool2) {
@@ -88,13 +105,9 @@ __device__ __forceinline__ void small_epilogue(const ConvArgs& a, f32x4_s acc, c
     v[2] += bf2f_s(f.res.y & 0xFFFFu);
     v[3] += bf2f_s(f.res.y >> 16);
   }
-  if (a.relu) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = fmaxf(v[j], 0.f);
-  }
   uint2 p;
-  p.x = f2bf_s(v[0]) | (f2bf_s(v[1]) << 16);
-  p.y = f2bf_s(v[2]) | (f2bf_s(v[3]) << 16);
+  p.x = pack2_s(v[0], v[1], a.relu, split);
+  p.y = pack2_s(v[2], v[3], a.relu, split);
   *(uint2*)((bf16_t*)a.y + o) = p;
 }
 
@@ -248,7 +261,7 @@ __global__ __launch_bounds__(small_waves(TMB * TNB) * 64) void conv_small_kernel
 #pragma unroll
       for (int b = 0; b < NBLK; ++b) {
         const int m = m0 + b / TNB * 16 + r, c = n0 + b % TNB * 16 + 4 * kc;
-        small_epilogue(a, acc[b / TNB][b % TNB], NBLK == 1 ? fold : small_fold(a, m, c), m, c);
+        small_epilogue(a, acc[b / TNB][b % TNB], NBLK == 1 ? fold : small_fold(a, m, c), m, c, false);
       }
       return;
     }
@@ -267,7 +280,8 @@ __global__ __launch_bounds__(small_waves(TMB * TNB) * 64) void conv_small_kernel
       }
     }
   }
-  if (wave < NBLK) small_epilogue(a, sum, fold, m0 + wave / TNB * 16 + r, n0 + wave % TNB * 16 + 4 * kc);
+  if (wave < NBLK) small_epilogue(a, sum, fold, m0 + wave / TNB * 16 + r, n0 + wave % TNB * 16 + 4 * kc,
+                                  true);
 }
 
 bool conv_small_fits(const ConvArgs& a, int tile) {

@@ -97,3 +97,36 @@ def test_wider_maps_stay_apart(monkeypatch):
     tile = len(tile_configs()) + 1
     assert sorted(r["layer"] for r in recs if r["tile_cfg"] == tile) == [3, 4, 7, 8]
     assert np.array_equal(z.view(np.uint32), apart.view(np.uint32))
+
+
+@pytest.mark.parametrize("mid, with_3x3", [(128, True), (256, False), (256, True), (64, True)])
+def test_fused_blocks_nonfinite(mid, with_3x3, monkeypatch):
+    """A positive NaN (of a layer's shift; arithmetic gives negative ones here) is kept by the ReLU of
+    an unsplit layer, an integer maximum, and made 0 by that of a split layer's reduce launch: a
+    unit does as the layers apart do.  The request holds an infinity and a NaN besides."""
+    L = [conv(-1, 8, 4 * mid, 1),                   # 0: residual
+         conv(-1, 8, mid, 1)]                       # 1: the unit's input
+    if with_3x3:
+        L.append(conv(1, mid, mid, 3))
+    L.append(conv(len(L) - 1, mid, 4 * mid, 1, res=0))
+    L.append(conv(len(L) - 1, 4 * mid, mid, 1))
+    L.append(Layer(op=GLOBAL_AVGPOOL, input=len(L) - 1, c_in=mid, c_out=mid))
+    L.append(Layer(op=FC, input=len(L) - 1, c_in=mid, c_out=24, bias=True))
+    spec = ModelSpec("nonfinite", L, 24, (8, 6, 7))
+    params = wl.gen_params(spec, 7, True, "random")
+    P = params.layers
+    batch = wl.gen_images(3, spec.input_shape, "normal", True, seed=mid).copy()
+    batch[1, 3, 0, 0], batch[2, 3, 0, 0] = np.inf, np.nan
+    x = torch.from_numpy(batch).to(DEV)
+    for at in range(2, len(L) - 2):     # each of the unit's layers in turn
+        P[at].bn_beta[5], beta = np.nan, P[at].bn_beta[5]
+        apart, r0 = logits(spec, params, x, 3, "0", monkeypatch)
+        splits = {r["layer"]: r["splits"] for r in r0 if r["kind"] == "conv_mfma"}
+        # (a product with a NaN is a negative one: only the last layer's can reach the logits)
+        assert np.isnan(apart[0]).any() == (at == len(L) - 3 and splits[at] == 1)
+        for mode in ("64", "32"):
+            z, _ = logits(spec, params, x, 3, mode, monkeypatch)
+            ok = ~np.isnan(apart)
+            assert np.array_equal(~np.isnan(z), ok), (at, mode)
+            assert np.array_equal(z[ok].view(np.uint32), apart[ok].view(np.uint32)), (at, mode)
+        P[at].bn_beta[5] = beta

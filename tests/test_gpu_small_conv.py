@@ -99,6 +99,33 @@ def test_small_tiles_bitwise(name, monkeypatch):
     assert np.abs(z0 - ref).max() <= 1e-2 * np.abs(ref).max()
 
 
+@pytest.mark.parametrize("c_in, k, split", [(64, 1, False), (64, 3, False), (256, 3, True)])
+def test_small_tiles_nonfinite(c_in, k, split, monkeypatch):
+    """A positive NaN (of a layer's shift; arithmetic gives negative ones here) ends as in the launches
+    that the tile stands for: kept by the unsplit kernel's ReLU, an integer maximum, and 0 after
+    the reduce launch's.  The request holds infinities and a NaN, the residual their opposites."""
+    L = [conv(-1, c_in, 96, 1, relu=False), conv(-1, c_in, 96, k, res=0),
+         Layer(op=GLOBAL_AVGPOOL, input=1, c_in=96, c_out=96),
+         Layer(op=FC, input=2, c_in=96, c_out=10, bias=True)]
+    spec = ModelSpec("nonfinite", L, 10, (c_in, 6, 7))
+    params = wl.gen_params(spec, 3, True, "random")
+    P = params.layers
+    P[0].weight[:, 3], P[1].weight[:, 3] = -1.0, 1.0
+    for p in P[:2]:
+        p.bn_gamma = np.abs(p.bn_gamma) + 0.1
+    P[1].bn_beta[5] = np.nan
+    batch = wl.gen_images(4, spec.input_shape, "normal", True, seed=2).copy()
+    batch[1:, 3, 0, 0] = np.inf, -np.inf, np.nan
+    x = torch.from_numpy(batch).to(DEV)
+    z0, _, r0 = run([spec], [params], x, 4, "0", monkeypatch)
+    assert any(r["splits"] > 1 for r in r0) == split and np.isnan(z0[0]).all() == (not split)
+    ok = ~np.isnan(z0)
+    for t in range(4):
+        z, _, _ = run([spec], [params], x, 4, str(t + 1), monkeypatch)
+        assert np.array_equal(np.isnan(z), np.isnan(z0)), t
+        assert np.array_equal(z[ok].view(np.uint32), z0[ok].view(np.uint32)), t
+
+
 @pytest.mark.parametrize("n, hw, c", [(1, (1, 1), 512), (3, (1, 3), 520), (2, (7, 7), 2048), (5, (8, 8), 648),
                                       (2, (5, 13), 512)])
 def test_small_mean_keeps_its_order(n, hw, c):
