@@ -184,6 +184,9 @@ struct rafiki_ensemble_s {
   // the direct kernel's persistent workgroups fill each compute unit's LDS, which leaves
   // no room for the other lane's workgroups while it runs.
   std::map<int, std::vector<std::vector<int>>> tuned_lean_gemm;
+  // Each layer's fastest GEMM tile: what grouped and paired launches run where `tuned` has a
+  // tile that is not for several members (shared_cfg).
+  std::map<int, std::vector<std::vector<int>>> tuned_gemm;
   // Per batch size, model and block unit: pixels per workgroup of its fused launch (0: the
   // layers run apart), whichever was faster when tuning.
   std::map<int, std::vector<std::vector<int>>> blocks;
@@ -1427,6 +1430,22 @@ constexpr int kCfgSmall = kCfgReduce + 1, kCfgPatch = kCfgSmall + kNumSmallTiles
 constexpr int kSmallMaxRows = 16384;
 constexpr int kBlockTiles[2] = {64, 32};
 
+// Whether tile cfg, tuned on launches of op over n requests by one member, also serves `members` of
+// them in one launch.  The direct and the patch kernel take one member.  The small tiles load
+// more bytes per output than the GEMM's and win by filling an idle chip, so they serve up to 8
+// waves per compute unit over all members (rows / tile x channels / tile x the waves of the
+// splits).  ResNet-50s in us per call, GEMM tiles only / this / small tiles always: two at one
+// image 436 / 426 / 421, at four 614 / 612 / 697, four at one image 518 / 518 / 628, at four
+// 994 / 985 / 1196; 16 waves per unit took 690, 592 and 985 in the last three.
+bool shared_cfg(const Op& op, int n, int members, int cfg) {
+  if (cfg < kCfgSmall) return cfg != kCfgDirect;
+  if (cfg >= kCfgPatch) return false;
+  const int* t = kSmallTiles[cfg - kCfgSmall];
+  const int rows = n * op.Ho * op.Wo, splits = choose_splits(rows, op.c_out, op.Kp / 64);
+  const long long tiles = (long long)((rows + t[0] - 1) / t[0]) * ((op.c_out + t[1] - 1) / t[1]);
+  return tiles * std::min(splits, t[0] * t[1] >= 1024 ? 8 : 16) * members <= 2048;
+}
+
 // A tile of the lean set: 8 waves, at least 128 x 128, K tiles of 64 (one barrier per 64
 // of K; the 32-wide tiles of the same footprint gained a third as much alongside other
 // models) and a ring of at most 64 KB.
@@ -1913,6 +1932,7 @@ int tune(rafiki_ensemble_s* e, int n, const void* in, hipStream_t s) {
   if (!timing) {
     e->tuned_lean[n] = choice;
     e->tuned_lean_gemm[n] = choice;
+    e->tuned_gemm[n] = choice;
     e->tuned[n] = std::move(choice);
     e->model_ms[n] = std::move(est);
     return RAFIKI_OK;
@@ -1966,15 +1986,17 @@ int tune(rafiki_ensemble_s* e, int n, const void* in, hipStream_t s) {
   e->force_tile = saved_force;
   e->trace.on = saved_trace;
   if (rc) return rc;
-  std::vector<std::vector<int>> lean(NM);
+  std::vector<std::vector<int>> lean(NM), gemm(NM);
   for (size_t mi = 0; mi < NM; ++mi) {
     est[mi] = 0.0;
     lean[mi] = choice[mi];
+    gemm[mi] = choice[mi];
     for (size_t oi = 0; oi < cand[mi].size(); ++oi) {
-      float t = 1e30f;
+      float t = 1e30f, tg = 1e30f;
       for (int cfg : cand[mi][oi]) {
         const float tc = op_time(e->models[mi].ops[oi], n, best[mi][oi], cfg);
         if (tc < t) { t = tc; choice[mi][oi] = cfg; }
+        if (tc < tg && cfg < kNumMfmaConfigs) { tg = tc; gemm[mi][oi] = cfg; }
       }
       if (t < 1e29f) est[mi] += t;
       const Op& op = e->models[mi].ops[oi];
@@ -1999,11 +2021,13 @@ int tune(rafiki_ensemble_s* e, int n, const void* in, hipStream_t s) {
     }
   e->tuned_lean_gemm[n] = std::move(lean_gemm);
   e->tuned_lean[n] = std::move(lean);
+  e->tuned_gemm[n] = std::move(gemm);
   e->tuned[n] = std::move(choice);
   rc = tune_blocks(e, n, in, s, best, est);
   if (rc) {
     e->tuned_lean_gemm.erase(n);
     e->tuned_lean.erase(n);
+    e->tuned_gemm.erase(n);
     e->tuned.erase(n);
     return rc;
   }
@@ -2021,7 +2045,8 @@ int tune(rafiki_ensemble_s* e, int n, const void* in, hipStream_t s) {
 // One op of several members in one launch: member k is op ois[k] of model mis[k]; every
 // member's op has the same launch signature (same_launch), so the launch shares shapes,
 // tile and K splits and each member's outputs are those of its own launch.  The tile
-// is member 0's tuned one (every tile gives the same sums).
+// is member 0's tuned one where it suits several members (shared_cfg), else its fastest
+// GEMM tile; every tile gives the same sums.
 int run_op(const rafiki_ensemble_s* e, const int* mis, const int* ois, int nm, const void* in, int n,
            float* const* logits, hipStream_t s, const CallScratch* ws) {
   if (nm < 1 || nm > kMaxGroup) return fail(RAFIKI_ERR_INVALID, "internal: group size");
@@ -2072,6 +2097,11 @@ int run_op(const rafiki_ensemble_s* e, const int* mis, const int* ois, int nm, c
           cfg = kCfgSmall + e->small_tiles - 1;
         }
         if (nm > 1) {
+          const bool forced = cfg >= kCfgSmall && cfg < kCfgPatch && e->small_tiles > 0;
+          if (!forced && !shared_cfg(op, n, nm, cfg)) {
+            const auto git = e->tuned_gemm.find(n);
+            cfg = git == e->tuned_gemm.end() ? -1 : git->second[mi][oi];
+          }
           a.n_members = nm;
           for (int k = 0; k < nm; ++k) {
             const Op& ok = mop(k);

@@ -17,7 +17,8 @@ import torch
 import envutil
 import oracle
 import workloads as wl
-from workloads import ModelSpec
+from workloads import Layer, ModelSpec, CONV2D, GLOBAL_AVGPOOL, FC
+from paper_1804_06087_amd.binding import tile_configs
 
 pytestmark = pytest.mark.gpu
 DEV = torch.device("cuda:0")
@@ -103,3 +104,64 @@ def test_mixed_ensemble_groups_only_identical_members():
     x = torch.from_numpy(batch).to(DEV)
     with make(specs, params, "bf16", 16, True) as g, make(specs, params, "bf16", 16, False) as u:
         assert len(launches(g, x, 16, 0b111, 10)) == len(launches(u, x, 16, 0b111, 10))
+
+
+def wide_layers(extra):
+    """Layers that run on the patch kernel and as a fused bottleneck block when a model runs alone;
+    `extra` appends one more 3x3 layer (another layer list: paired instead of grouped)."""
+    conv = lambda i, ci, co, k, res=-1: Layer(op=CONV2D, input=i, input2=res, c_in=ci, c_out=co, kh=k, kw=k, stride=1,  # noqa: E731
+                                              pad=k // 2, relu=True, bn=True)
+    L = [conv(-1, 8, 128, 1), conv(0, 128, 256, 3), conv(1, 256, 256, 3), conv(2, 256, 256, 3),
+         conv(3, 256, 64, 1), conv(4, 64, 64, 3), conv(5, 64, 256, 1, res=3), conv(6, 256, 64, 1)]
+    if extra:
+        L.append(conv(7, 64, 64, 3))
+    L.append(Layer(op=GLOBAL_AVGPOOL, input=len(L) - 1, c_in=64, c_out=64))
+    L.append(Layer(op=FC, input=len(L) - 1, c_in=64, c_out=10, bias=True))
+    return ModelSpec("wide", L, 10, (8, 28, 28))
+
+
+def check_shared_tiles(alone, together):
+    """The layers that run on the patch kernel alone run on a tuned tile of the GEMM together, not
+    on the untuned default (64 x 128, far from the fastest for these shapes)."""
+    gemm = len(tile_configs())
+    patch = {r["layer"] for r in alone if r["kind"] == "conv_mfma" and r["tile_cfg"] >= gemm + 8}
+    tiles = [r["tile_cfg"] for r in together if r["kind"] == "conv_mfma" and r["layer"] in patch]
+    assert all(t < gemm or gemm + 4 <= t < gemm + 8 for t in tiles)
+    if patch:
+        assert any(t != 6 for t in tiles), tiles
+
+
+def test_grouped_patch_and_block_layers(monkeypatch):
+    """Two members with patch and bottleneck layers: their own launches' bits, on tuned tiles."""
+    spec = wide_layers(False)
+    params = [wl.gen_params(spec, s, True, "random") for s in (3, 4)]
+    batch = wl.gen_images(24, spec.input_shape, "normal", True, seed=5)
+    check_pair([spec] * 2, params, batch, "bf16", [24, 3], [0b11], 10, 24)
+    monkeypatch.setenv("RAFIKI_FUSED_BLOCKS", "64")
+    check_pair([spec] * 2, params, batch, "bf16", [24, 3], [0b11], 10, 24)
+    monkeypatch.delenv("RAFIKI_FUSED_BLOCKS")
+    x = torch.from_numpy(batch).to(DEV)
+    with make([spec] * 2, params, "bf16", 24, True) as g:
+        check_shared_tiles(launches(g, x, 24, 0b01, 10), launches(g, x, 24, 0b11, 10))
+
+
+def test_paired_patch_and_block_layers():
+    """The same of two models with different layer lists on one lane."""
+    specs = [wide_layers(False), wide_layers(True)]
+    params = [wl.gen_params(s, 3 + k, True, "random") for k, s in enumerate(specs)]
+    batch = wl.gen_images(24, specs[0].input_shape, "normal", True, seed=6)
+    x = torch.from_numpy(batch).to(DEV)
+    with make(specs, params, "bf16", 24, True) as ens:
+        assert ens.pairing(0, 1) >= 8
+        for n in (24, 3):
+            ens.set_schedule(n, 0b11, -1, 0)
+            p0, l0 = run(ens, x, n, 0b11, 10)
+            ens.set_schedule_pair(n, 0b11, 0, 1)
+            for _ in range(2):
+                p, lab = run(ens, x, n, 0b11, 10)
+                assert np.array_equal(p, p0) and np.array_equal(lab, l0), n
+        alone = launches(ens, x, 24, 0b01, 10)
+        ens.trace(True, concurrent=True)
+        run(ens, x, 24, 0b11, 10)
+        check_shared_tiles(alone, ens.trace_read())
+        ens.trace(False)
