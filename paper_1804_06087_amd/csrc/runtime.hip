@@ -1806,12 +1806,14 @@ inline int run_model(const rafiki_ensemble_s* e, int mi, const void* in, int n, 
 }
 
 // Time of op's launches with tile cfg, from the tuner's shortest launches `best`: a split
-// launch of the tiled kernel is followed by its reduce launch.  Each launch beyond the first
+// launch of the tiled kernel is followed by its reduce launch, if one was seen (fused branches
+// of one channel block run unsplit).  Each launch beyond the first
 // counts kLaunchGapMs, the time between two dependent launches of a stream beyond their own
 // execution (a chain of empty launches takes 2.6 us each, of which about 1 us is execution).
 constexpr float kLaunchGapMs = 0.0015f;
 float op_time(const Op& op, int n, const std::vector<float>& best, int cfg) {
-  const bool reduce = cfg < kNumMfmaConfigs && choose_splits(n * op.Ho * op.Wo, op.c_out, op.Kp / 64) > 1;
+  const bool reduce = cfg < kNumMfmaConfigs && best[kCfgReduce] < 1e29f &&
+                      choose_splits(n * op.Ho * op.Wo, op.c_out, op.Kp / 64) > 1;
   return best[cfg] + (reduce ? best[kCfgReduce] + kLaunchGapMs : 0.f);
 }
 

@@ -273,6 +273,26 @@ def test_fused_branches_tile_independent(n, case):
     check_bf16_tensor(base, ref)
 
 
+def test_fused_branches_of_one_channel_block_are_tuned():
+    """Branches over 64 channels with 12 and more taps: the shape would split K, but a split takes
+    whole channel blocks and there is one, so the GEMM runs unsplit without a reduce launch.  Its
+    tile is tuned like any other (not left at 64 x 128 for every batch size)."""
+    spec, params = _branch_probe(dim=64, seq_len=40, filters=(100, 90), widths=(12, 14))
+    tiles = []
+    with Ensemble([spec], [params], precision="bf16", max_batch=32) as ens:
+        for n in (1, 2, 3, 5, 8, 16, 32):
+            x = torch.from_numpy(wl.gen_tokens(n, 40, 97, seed=n)).to(DEV)
+            out = torch.empty((n, spec.n_classes), dtype=torch.float32, device=DEV)
+            ens.model_logits(0, x, n, out)
+            ens.trace(True)
+            ens.model_logits(0, x, n, out)
+            recs = [r for r in ens.trace_read() if r["kind"] in ("conv_mfma", "splitk_reduce")]
+            ens.trace(False)
+            assert all(r["splits"] == 1 for r in recs)
+            tiles.append(recs[0]["tile_cfg"])
+    assert any(t != 6 for t in tiles), tiles
+
+
 def test_invalid_token_ids_read_zero_rows(monkeypatch):
     """Token ids outside [0, vocab) read a zero embedding row, both in the embedding
     kernel (branches apart) and in the GEMM that gathers the rows itself (fused)."""
