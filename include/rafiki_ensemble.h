@@ -139,7 +139,12 @@ typedef struct {
  * embedding of at least 1024 rows and 192 channels, their products are taken once at
  * create, into an fp32 table [vocab][sum of kw x filters] of at most 4 MiB per request of
  * max_batch, and a request sums table rows instead (fp32, each tap's sum over the channels
- * first, then the taps in order).
+ * first, then the taps in order).  These sums round differently from the GEMM's (features
+ * may differ by one bf16 step), so handles of different max_batch may; RAFIKI_TAP_TABLE at
+ * create fixes the choice (0: never a table, 1: whatever max_batch is).
+ * Where the device's memory does not hold everything (or RAFIKI_DEVICE_MB at create caps
+ * it), a handle does without the tables (unless RAFIKI_TAP_TABLE=1) and without the
+ * second copies of weights that the fused bottleneck and patch launches read.
  * In fp32, a model's leading stride-1 "same" 1x1 and 3x3 convolutions and 2x2 max-pools run
  * as one launch that reads the request itself (when every model of the handle starts with
  * at least two such layers; as many of them as pay at the call's n), and the mean over positions with the final FC as another

@@ -201,6 +201,12 @@ struct rafiki_ensemble_s {
   // on every layer it takes, unset (-1) the faster when tuning
   int small_tiles = -1;
   int patch_tiles = -1;             // RAFIKI_PATCH_TILES: the same for the patch kernel's tiles
+  // RAFIKI_TAP_TABLE at create: 0 never, 1 whatever max_batch is, unset (-1) by build_tap_table's rule
+  int tap_tables = -1;
+  // What a handle can do without where memory is short: tap tables (unless RAFIKI_TAP_TABLE=1) and
+  // the weights once more in the fused block's and the patch kernel's order.
+  bool extras = true;
+  size_t mem_used = 0, mem_cap = 0;   // device bytes allocated; RAFIKI_DEVICE_MB at create (0: no cap)
   // Per batch size: each model's forward time alone, estimated when tuning (sum of the
   // chosen tiles' times; GEMM FLOPs / 1e12 when tiles are not timed).
   std::map<int, std::vector<double>> model_ms;
@@ -273,11 +279,19 @@ struct rafiki_ensemble_s {
 
 namespace {
 
+hipError_t device_malloc(rafiki_ensemble_s* e, void** p, size_t bytes) {
+  *p = nullptr;
+  if (e->mem_cap && bytes > e->mem_cap - std::min(e->mem_cap, e->mem_used)) return hipErrorOutOfMemory;
+  const hipError_t st = hipMalloc(p, bytes);
+  if (st == hipSuccess) e->mem_used += bytes;
+  return st;
+}
+
 int dev_alloc(rafiki_ensemble_s* e, void** p, size_t bytes) {
   *p = nullptr;
   if (e->dry) return RAFIKI_OK;
   if (bytes == 0) bytes = 256;
-  hipError_t st = hipMalloc(p, bytes);
+  hipError_t st = device_malloc(e, p, bytes);
   if (st != hipSuccess) {
     *p = nullptr;
     (void)hipGetLastError();
@@ -573,7 +587,7 @@ int fuse_branches(rafiki_ensemble_s* e, const rafiki_model_desc& md, Model& M, c
 int find_blocks(rafiki_ensemble_s* e, const rafiki_model_desc& md, Model& M) {
   M.units.clear();
   M.unit_of.assign(M.ops.size(), -1);
-  if (e->precision != RAFIKI_BF16 || !e->fused_blocks) return RAFIKI_OK;
+  if (e->precision != RAFIKI_BF16 || !e->fused_blocks || !e->extras) return RAFIKI_OK;
   std::vector<int> readers(M.tensors.size(), 0);
   for (const Op& op : M.ops)
     for (int src : {op.in, op.in2})
@@ -639,7 +653,7 @@ int find_blocks(rafiki_ensemble_s* e, const rafiki_model_desc& md, Model& M) {
 // convolutions without residual over 64 q channels to 128 p) unless the handle is in its
 // validation pass.
 int pack_patches(rafiki_ensemble_s* e, Model& M) {
-  if (e->precision != RAFIKI_BF16 || e->dry || e->patch_tiles == 0) return RAFIKI_OK;
+  if (e->precision != RAFIKI_BF16 || e->dry || e->patch_tiles == 0 || !e->extras) return RAFIKI_OK;
   bool any = false;
   for (Op& op : M.ops) {
     if (op.kind != O_CONV || op.in2 >= 0 || op.in < 0 || op.kh != 3 || op.kw != 3 || op.stride != 1 || op.pad != 1 ||
@@ -785,7 +799,9 @@ void find_chain(rafiki_ensemble_s* e, const rafiki_model_desc& md, Model& M) {
 // kTapBytesPerRequest per request the handle serves (a handle for a few requests does not
 // hold 146 MB per model for them), and vocabularies under kTapMinVocab rows, smaller than any
 // text model's, keep the GEMM, whose outputs are bitwise those of the separate branches.
-// A table that does not fit in memory is not an error: the GEMM serves.
+// A table that does not fit in memory is not an error: the GEMM serves (and create starts
+// again without tables where a table left too little for the rest).  RAFIKI_TAP_TABLE=1 asks for
+// the table whatever max_batch is, and a table that does not fit is then an error.
 constexpr int kTapMinChannels = 192, kTapMinVocab = 1024;
 constexpr long long kTapBytesPerRequest = 4LL << 20;
 int build_tap_table(rafiki_ensemble_s* e, const rafiki_model_desc& md, Op& op, const BranchGroup& g,
@@ -799,8 +815,10 @@ int build_tap_table(rafiki_ensemble_s* e, const rafiki_model_desc& md, Op& op, c
   }
   const int ldt = round_up(rows, 32);
   const long long bytes = (long long)(e->vocab + 1) * ldt * 4;
-  if (op.cin_l < kTapMinChannels || e->vocab < kTapMinVocab || bytes > kTapBytesPerRequest * e->max_batch ||
-      bytes >= (1LL << 32) || (long long)e->vocab * op.Cs_in * 2 >= (1LL << 31) || quads > kTapThreads || kw_max > 8 || op.W > kTapMaxLen)
+  const bool asked = e->tap_tables > 0;
+  if (e->tap_tables == 0 || (!asked && (!e->extras || bytes > kTapBytesPerRequest * e->max_batch))) return RAFIKI_OK;
+  if (op.cin_l < kTapMinChannels || e->vocab < kTapMinVocab || bytes >= (1LL << 32) ||
+      (long long)e->vocab * op.Cs_in * 2 >= (1LL << 31) || quads > kTapThreads || kw_max > 8 || op.W > kTapMaxLen)
     return RAFIKI_OK;
   // the products as a GEMM: embedding rows x (branch, tap, filter) rows
   const int Kp = round_up(op.Cs_in, 64), Co_pad = round_up(rows, kCoPadBf16);
@@ -818,12 +836,13 @@ int build_tap_table(rafiki_ensemble_s* e, const rafiki_model_desc& md, Op& op, c
   std::vector<float> fold((size_t)2 * Co_pad, 0.f);
   std::fill(fold.begin(), fold.begin() + Co_pad, 1.f);
   void *dw = nullptr, *df = nullptr, *dt = nullptr;
-  hipError_t st = hipMalloc(&dt, (size_t)bytes);
-  if (st == hipSuccess) st = hipMalloc(&dw, w.size() * 2);
-  if (st == hipSuccess) st = hipMalloc(&df, fold.size() * 4);
+  hipError_t st = device_malloc(e, &dt, (size_t)bytes);
+  const size_t kept = e->mem_used;
+  if (st == hipSuccess) st = device_malloc(e, &dw, w.size() * 2);
+  if (st == hipSuccess) st = device_malloc(e, &df, fold.size() * 4);
   unsigned* slot = nullptr;
   const size_t slot_bytes = (size_t)e->max_batch * round_up(op.c_out, 8) * 4;
-  if (st == hipSuccess && !op.d_slot) st = hipMalloc((void**)&slot, slot_bytes);
+  if (st == hipSuccess && !op.d_slot) st = device_malloc(e, (void**)&slot, slot_bytes);
   if (st == hipSuccess) st = hipMemcpy(dw, w.data(), w.size() * 2, hipMemcpyHostToDevice);
   if (st == hipSuccess) st = hipMemcpy(df, fold.data(), fold.size() * 4, hipMemcpyHostToDevice);
   if (st == hipSuccess) st = hipMemset(dt, 0, (size_t)bytes);
@@ -843,9 +862,18 @@ int build_tap_table(rafiki_ensemble_s* e, const rafiki_model_desc& md, Op& op, c
   if (st == hipSuccess) st = hipStreamSynchronize(nullptr);
   if (dw) (void)hipFree(dw);
   if (df) (void)hipFree(df);
+  e->mem_used = kept + (slot ? slot_bytes : 0);
   if (st != hipSuccess) {
-    if (dt) (void)hipFree(dt);
-    if (slot) (void)hipFree(slot);
+    if (dt) {
+      (void)hipFree(dt);
+      e->mem_used -= (size_t)bytes;
+    }
+    if (slot) {
+      (void)hipFree(slot);
+      e->mem_used -= slot_bytes;
+    }
+    if (st == hipErrorOutOfMemory && asked)
+      return fail(RAFIKI_ERR_NOMEM, "tap table of " + std::to_string(bytes) + " bytes: out of memory");
     if (st != hipErrorOutOfMemory) return fail(RAFIKI_ERR_HIP, std::string("tap table: ") + hipGetErrorString(st));
     (void)hipGetLastError();
     return RAFIKI_OK;
@@ -1113,7 +1141,7 @@ int build_model(rafiki_ensemble_s* e, int mi, const rafiki_model_desc& md, Model
     }
     st.out = op.out;
     if (!y.is_logits) st.out_bytes = nb * y.item_elems() * es;
-    if (op.kind == O_CONV1D) st.scratch_bytes = nb * op.Wo * round_up(op.c_out, 8) * es;
+    if (op.kind == O_CONV1D && !op.d_taps) st.scratch_bytes = nb * op.Wo * round_up(op.c_out, 8) * es;
     st.last = M.unit_of[i] >= 0 ? M.units[M.unit_of[i]].last : (int)i;
   }
   const ArenaPlan plan = plan_arena(steps, (int)M.tensors.size());
@@ -2436,10 +2464,9 @@ __global__ void zero_u32_kernel(unsigned* p, long long count) {
 
 extern "C" {
 
-int rafiki_ensemble_create(const rafiki_model_desc* models, int n_models, const rafiki_ensemble_opts* opts,
-                           rafiki_ensemble_t* out) {
-  if (out) *out = nullptr;
-  if (!models || !opts || !out) return fail(RAFIKI_ERR_INVALID, "null argument");
+// One attempt at rafiki_ensemble_create; extras: with what the handle can do without.
+static int create_handle(const rafiki_model_desc* models, int n_models, const rafiki_ensemble_opts* opts, bool extras,
+                         rafiki_ensemble_t* out) {
   if (n_models < 1 || n_models > 32) return fail(RAFIKI_ERR_INVALID, "n_models must be in [1, 32]");
   if (opts->precision != RAFIKI_FP32 && opts->precision != RAFIKI_BF16)
     return fail(RAFIKI_ERR_INVALID, "unknown precision");
@@ -2458,6 +2485,7 @@ int rafiki_ensemble_create(const rafiki_model_desc* models, int n_models, const 
   if (n_classes > 1024) return fail(RAFIKI_ERR_UNSUPPORTED, "at most 1024 classes are supported");
 
   std::unique_ptr<rafiki_ensemble_s> e(new rafiki_ensemble_s());
+  e->extras = extras;
   e->n_models = n_models; e->n_classes = n_classes; e->precision = opts->precision;
   e->max_batch = opts->max_batch; e->input_kind = opts->input_kind;
   e->C = opts->c; e->H = opts->h; e->W = opts->w; e->vocab = opts->vocab;
@@ -2475,6 +2503,8 @@ int rafiki_ensemble_create(const rafiki_model_desc* models, int n_models, const 
   if (const char* t = std::getenv("RAFIKI_CHAINS")) e->chains = std::atoi(t) != 0;
   if (const char* t = std::getenv("RAFIKI_PATCH_TILES")) e->patch_tiles = std::min(std::atoi(t), kNumPatchTiles);
   if (const char* t = std::getenv("RAFIKI_SMALL_TILES")) e->small_tiles = std::min(std::atoi(t), kNumSmallTiles);
+  if (const char* t = std::getenv("RAFIKI_TAP_TABLE")) e->tap_tables = std::atoi(t) != 0;
+  if (const char* t = std::getenv("RAFIKI_DEVICE_MB")) e->mem_cap = (size_t)std::max(0, std::atoi(t)) << 20;
   // Pass 1: validate every model and infer shapes without touching the device.
   e->dry = true;
   e->models.resize(n_models);
@@ -2567,6 +2597,14 @@ int rafiki_ensemble_create(const rafiki_model_desc* models, int n_models, const 
   *out = e.release();
   g_err.clear();
   return RAFIKI_OK;
+}
+
+int rafiki_ensemble_create(const rafiki_model_desc* models, int n_models, const rafiki_ensemble_opts* opts,
+                           rafiki_ensemble_t* out) {
+  if (out) *out = nullptr;
+  if (!models || !opts || !out) return fail(RAFIKI_ERR_INVALID, "null argument");
+  const int rc = create_handle(models, n_models, opts, true, out);
+  return rc == RAFIKI_ERR_NOMEM ? create_handle(models, n_models, opts, false, out) : rc;
 }
 
 }  // extern "C"

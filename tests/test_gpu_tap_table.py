@@ -14,7 +14,7 @@ import torch
 import oracle
 import workloads as wl
 from workloads import Layer, ModelSpec, FC, EMBEDDING, CONV1D_MAXTIME, CONCAT
-from paper_1804_06087_amd import Ensemble
+from paper_1804_06087_amd import Ensemble, RafikiError, RAFIKI_ERR_NOMEM
 
 pytestmark = pytest.mark.gpu
 DEV = torch.device("cuda:0")
@@ -131,3 +131,58 @@ def test_small_vocabulary_and_small_handle_keep_the_gemm():
         spec, params = probe(seq_len=20, filters=(100, 100), widths=(3, 4), **kw)
         _, kinds, _ = run([spec], [params], wl.gen_tokens(2, 20, kw["vocab"], seed=1), mb)
         assert "tap_table" not in kinds, kw
+
+
+def test_tap_table_switch(monkeypatch):
+    """RAFIKI_TAP_TABLE fixes the choice that otherwise depends on max_batch: 1 builds the table for
+    a handle of two requests, and the features are those of a larger handle's table bit for bit."""
+    case = dict(vocab=30000, dim=192, seq_len=20, filters=(100, 100), widths=(3, 4))
+    spec, params = probe(**case)
+    tok = wl.gen_tokens(2, 20, 30000, seed=1)
+    out = {}
+    for mode, mb in (("1", 2), ("1", 64), ("0", 64)):
+        monkeypatch.setenv("RAFIKI_TAP_TABLE", mode)
+        zs, kinds, _ = run([spec], [params], tok, mb)
+        assert ("tap_table" in kinds) == (mode == "1")
+        out[mode, mb] = zs[0]
+    assert np.array_equal(out["1", 2].view(np.uint32), out["1", 64].view(np.uint32))
+    check(out["1", 2], out["0", 64])
+
+
+def test_tables_never_cost_a_handle(monkeypatch):
+    """A handle that fits in memory without tables is created whatever the tables would take: under
+    every cap from the smallest that the GEMM alone needs, create succeeds."""
+    # a table of 97 MB, more than the arena and workspace of a model without one
+    case = dict(vocab=20000, dim=200, seq_len=256, filters=(100, 100, 100), widths=(3, 4, 5))
+    models = [probe(seed=s, **case) for s in (5, 6)]
+    specs, params = [m[0] for m in models], [m[1] for m in models]
+    tok = wl.gen_tokens(3, 256, 20000, seed=1)
+
+    def handle(cap, mode):
+        monkeypatch.setenv("RAFIKI_DEVICE_MB", str(cap))
+        if mode is None:
+            monkeypatch.delenv("RAFIKI_TAP_TABLE", raising=False)
+        else:
+            monkeypatch.setenv("RAFIKI_TAP_TABLE", mode)
+        return run(specs, params, tok, 64)
+
+    need = 8
+    while True:
+        try:
+            ref, kinds, _ = handle(need, "0")
+            break
+        except RafikiError as e:
+            assert e.code == RAFIKI_ERR_NOMEM
+            need += 2
+            assert need < 400
+    assert 8 < need < 140 and "tap_table" not in kinds
+    seen = set()
+    for cap in range(need, 260, 6):
+        zs, kinds, _ = handle(cap, None)
+        seen.add("tap_table" in kinds)
+        for z, r in zip(zs, ref):
+            check(z, r)
+    assert seen == {False, True}
+    with pytest.raises(RafikiError) as ei:
+        handle(8, "1")
+    assert ei.value.code == RAFIKI_ERR_NOMEM
