@@ -801,7 +801,9 @@ void find_chain(rafiki_ensemble_s* e, const rafiki_model_desc& md, Model& M) {
 // text model's, keep the GEMM, whose outputs are bitwise those of the separate branches.
 // A table that does not fit in memory is not an error: the GEMM serves (and create starts
 // again without tables where a table left too little for the rest).  RAFIKI_TAP_TABLE=1 asks for
-// the table whatever max_batch is, and a table that does not fit is then an error.
+// the table whatever max_batch is, and a table that does not fit is then an error.  The
+// table's maximum passes NaNs over where the GEMM's ReLU may keep them, so it takes finite
+// parameters only.
 constexpr int kTapMinChannels = 192, kTapMinVocab = 1024;
 constexpr long long kTapBytesPerRequest = 4LL << 20;
 int build_tap_table(rafiki_ensemble_s* e, const rafiki_model_desc& md, Op& op, const BranchGroup& g,
@@ -820,6 +822,17 @@ int build_tap_table(rafiki_ensemble_s* e, const rafiki_model_desc& md, Op& op, c
   if (op.cin_l < kTapMinChannels || e->vocab < kTapMinVocab || bytes >= (1LL << 32) ||
       (long long)e->vocab * op.Cs_in * 2 >= (1LL << 31) || quads > kTapThreads || kw_max > 8 || op.W > kTapMaxLen)
     return RAFIKI_OK;
+  const rafiki_layer& emb = md.layers[md.layers[g.branches[0]].input];
+  bool finite = true;
+  for (size_t k = 0; k < (size_t)e->vocab * op.cin_l; ++k) finite = finite && std::isfinite(emb.weight[k]);
+  for (int b : g.branches) {
+    const rafiki_layer& L = md.layers[b];
+    std::vector<float> fold(2 * (size_t)L.c_out);
+    fold_into(L, fold.data(), fold.data() + L.c_out);
+    for (float f : fold) finite = finite && std::isfinite(f);
+    for (size_t k = 0; k < (size_t)L.c_out * L.c_in * L.kw; ++k) finite = finite && std::isfinite(L.weight[k]);
+  }
+  if (!finite) return RAFIKI_OK;
   // the products as a GEMM: embedding rows x (branch, tap, filter) rows
   const int Kp = round_up(op.Cs_in, 64), Co_pad = round_up(rows, kCoPadBf16);
   std::vector<uint16_t> w((size_t)Co_pad * Kp, 0);

@@ -126,6 +126,31 @@ def test_tap_table_invalid_ids_and_group():
     assert np.abs(probs - sum(soft) / 2).max() <= 1e-6     # the grouped launch: fp32 softmax of the same logits
 
 
+@pytest.mark.parametrize("where", ["bias", "weight", "embedding"])
+def test_nonfinite_parameters_keep_the_gemm(where, monkeypatch):
+    """The table's maximum would pass a NaN over where the unsplit GEMM's ReLU keeps it."""
+    spec, params = probe(vocab=1100, dim=200, seq_len=20, filters=(10, 6), widths=(2, 5))
+    if where == "embedding":
+        params.layers[0].weight[7, 3] = np.inf
+    elif where == "weight":
+        params.layers[1].weight.reshape(-1)[5] = np.nan
+    else:
+        params.layers[2].bias[3] = np.nan
+    tok = wl.gen_tokens(64, 20, 1100, seed=3)
+    out = []
+    for mode in ("1", "0"):
+        monkeypatch.setenv("RAFIKI_TAP_TABLE", mode)
+        with Ensemble([spec], [params], precision="bf16", max_batch=64) as ens:
+            x = torch.from_numpy(tok).to(DEV)
+            z = torch.empty((64, spec.n_classes), dtype=torch.float32, device=DEV)
+            ens.trace(True)
+            ens.model_logits(0, x, 64, z)
+            assert "tap_table" not in [r["kind"] for r in ens.trace_read()]
+            ens.trace(False)
+            out.append(z.cpu().numpy())
+    assert np.array_equal(out[0].view(np.uint32), out[1].view(np.uint32))
+
+
 def test_small_vocabulary_and_small_handle_keep_the_gemm():
     for kw, mb in ((dict(vocab=1023, dim=300), 64), (dict(vocab=2000, dim=184), 64), (dict(vocab=30000, dim=192), 2)):
         spec, params = probe(seq_len=20, filters=(100, 100), widths=(3, 4), **kw)
