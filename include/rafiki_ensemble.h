@@ -126,7 +126,7 @@ typedef struct {
  * residual, the next block's 1x1 reduction; all with ReLU) may run as one launch, which
  * the tuner times against the layers apart; outputs are bitwise the same (environment
  * RAFIKI_FUSED_BLOCKS at create: 0 always apart, 32 or 64 always fused with that many
- * pixels per workgroup).  Layers of few output rows may run in small tiles whose
+ * pixels per workgroup, also with RAFIKI_AUTOTUNE=0; otherwise as timed).  Layers of few output rows may run in small tiles whose
  * workgroups sum their own K splits, timed the same way and bitwise the same
  * (RAFIKI_SMALL_TILES at create: 0 never, 1 to 4 one tile wherever it applies), and 3x3
  * layers of many channels from an input patch and streamed weights (RAFIKI_PATCH_TILES: 0

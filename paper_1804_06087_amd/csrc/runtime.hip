@@ -190,8 +190,8 @@ struct rafiki_ensemble_s {
   // Per batch size, model and block unit: pixels per workgroup of its fused launch (0: the
   // layers run apart), whichever was faster when tuning.
   std::map<int, std::vector<std::vector<int>>> blocks;
-  // RAFIKI_FUSED_BLOCKS at create: 0 the layers always apart, 1 the faster when tuning, 32 or
-  // 64 always fused with that many pixels per workgroup
+  // RAFIKI_FUSED_BLOCKS at create: 0 the layers always apart, 32 or 64 always fused with that many
+  // pixels per workgroup, otherwise (1) the faster when tuning
   int fused_blocks = 1;
   bool chains = true;               // fp32 runs of layers in one launch (RAFIKI_CHAINS=0 at create: never)
   bool raw_input = false;           // every model's chain reads the request itself: no staging
@@ -588,6 +588,7 @@ int find_blocks(rafiki_ensemble_s* e, const rafiki_model_desc& md, Model& M) {
   M.units.clear();
   M.unit_of.assign(M.ops.size(), -1);
   if (e->precision != RAFIKI_BF16 || !e->fused_blocks || !e->extras) return RAFIKI_OK;
+  if (!e->autotune && e->fused_blocks == 1) return RAFIKI_OK;   // nothing would choose them
   std::vector<int> readers(M.tensors.size(), 0);
   for (const Op& op : M.ops)
     for (int src : {op.in, op.in2})
@@ -654,6 +655,7 @@ int find_blocks(rafiki_ensemble_s* e, const rafiki_model_desc& md, Model& M) {
 // validation pass.
 int pack_patches(rafiki_ensemble_s* e, Model& M) {
   if (e->precision != RAFIKI_BF16 || e->dry || e->patch_tiles == 0 || !e->extras) return RAFIKI_OK;
+  if (!e->autotune && e->patch_tiles < 0) return RAFIKI_OK;   // nothing would choose them
   bool any = false;
   for (Op& op : M.ops) {
     if (op.kind != O_CONV || op.in2 >= 0 || op.in < 0 || op.kh != 3 || op.kw != 3 || op.stride != 1 || op.pad != 1 ||
@@ -1978,6 +1980,11 @@ int tune(rafiki_ensemble_s* e, int n, const void* in, hipStream_t s) {
     e->tuned_gemm[n] = choice;
     e->tuned[n] = std::move(choice);
     e->model_ms[n] = std::move(est);
+    if (e->fused_blocks > 1) {   // always fused
+      std::vector<std::vector<int>> always(NM);
+      for (size_t mi = 0; mi < NM; ++mi) always[mi].assign(e->models[mi].units.size(), e->fused_blocks);
+      e->blocks[n] = std::move(always);
+    }
     return RAFIKI_OK;
   }
   // best[mi][oi][cfg]: shortest launch seen.  A forced tile and the caller's tracing
@@ -2512,7 +2519,10 @@ static int create_handle(const rafiki_model_desc* models, int n_models, const ra
   if (const char* t = std::getenv("RAFIKI_LEAN_TILES")) e->lean_policy = std::atoi(t) != 0;
   if (const char* t = std::getenv("RAFIKI_GROUPED")) e->grouped = std::atoi(t) != 0;
   if (const char* t = std::getenv("RAFIKI_FUSED_NET")) e->fused_net = std::atoi(t) != 0;
-  if (const char* t = std::getenv("RAFIKI_FUSED_BLOCKS")) e->fused_blocks = std::atoi(t);
+  if (const char* t = std::getenv("RAFIKI_FUSED_BLOCKS")) {
+    const int v = std::atoi(t);
+    e->fused_blocks = v == 0 || v == kBlockTiles[0] || v == kBlockTiles[1] ? v : 1;
+  }
   if (const char* t = std::getenv("RAFIKI_CHAINS")) e->chains = std::atoi(t) != 0;
   if (const char* t = std::getenv("RAFIKI_PATCH_TILES")) e->patch_tiles = std::min(std::atoi(t), kNumPatchTiles);
   if (const char* t = std::getenv("RAFIKI_SMALL_TILES")) e->small_tiles = std::min(std::atoi(t), kNumSmallTiles);

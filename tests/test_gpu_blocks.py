@@ -86,6 +86,26 @@ def test_fused_blocks_bitwise(mid, hw, n, monkeypatch):
         assert np.abs(apart - ref).max() <= 2e-2 * np.abs(ref).max()
 
 
+def test_forced_without_tuning(monkeypatch):
+    """RAFIKI_FUSED_BLOCKS=32 / 64 fuse every unit with RAFIKI_AUTOTUNE=0 as well; without it, or with
+    any other value, an untuned handle runs the layers apart.  A tuned one takes other values as 1."""
+    spec = chain(128, (7, 9))
+    params = wl.gen_params(spec, 5, True, "random")
+    x = torch.from_numpy(wl.gen_images(3, spec.input_shape, "normal", True, seed=2)).to(DEV)
+    base = len(tile_configs())
+    monkeypatch.setenv("RAFIKI_AUTOTUNE", "0")
+    apart, _ = logits(spec, params, x, 3, "0", monkeypatch)
+    for mode, tile in (("64", base + 1), ("32", base + 2), ("1", None), ("16", None), ("128", None)):
+        z, recs = logits(spec, params, x, 3, mode, monkeypatch)
+        fused = sorted(r["layer"] for r in recs if r["tile_cfg"] in (base + 1, base + 2))
+        assert fused == ([2, 3, 4, 7, 8, 9, 10] if tile else []), mode
+        assert all(r["tile_cfg"] == tile for r in recs if r["layer"] in fused)
+        assert np.array_equal(z.view(np.uint32), apart.view(np.uint32)), mode
+    monkeypatch.delenv("RAFIKI_AUTOTUNE")
+    z, _ = logits(spec, params, x, 3, "128", monkeypatch)
+    assert np.array_equal(z.view(np.uint32), apart.view(np.uint32))
+
+
 def test_wider_maps_stay_apart(monkeypatch):
     """A map wider than the patch allows keeps its 3x3 apart; expansion and reduction still fuse."""
     spec = chain(256, (3, 30))
