@@ -89,3 +89,17 @@ def test_source_hash_ignores_comments_not_code():
     assert bench.strip_comments(src) != bench.strip_comments(src.replace("a + 1", "a + 2"))
     assert "add one" not in bench.strip_comments(src) and "sum" not in bench.strip_comments(src)
 
+
+
+def test_fused_launches_count_once():
+    """A fused bottleneck launch has a record per layer; its expansion, the one with a residual,
+    counts for it.  Other records are launches of their own."""
+    import workloads as wl
+    spec = wl.resnet50()
+    n = 40
+    expansions = [i for i, L in enumerate(spec.layers) if L.input2 >= 0]
+    a, b = expansions[1], expansions[2]
+    recs = [dict(model=0, layer=k, tile_cfg=n + 1) for k in (a - 1, a, a + 1)]      # one unit of three layers
+    recs += [dict(model=0, layer=k, tile_cfg=n + 2) for k in (b - 1, b)]            # one of two
+    recs += [dict(model=0, layer=k, tile_cfg=t) for k, t in ((a, 5), (a, n), (a, n + 8))] + [dict(model=-1, layer=-1, tile_cfg=-1)]
+    assert bench.launch_count(recs, [spec], n) == 6
