@@ -49,6 +49,7 @@ CASES = {
     "odd": ([conv(-1, 1, 5, 3), pool(0, 5), conv(1, 5, 12, 3, relu=False), conv(2, 12, 9, 1)], (1, 11, 7)),
     "pool_last": ([conv(-1, 3, 6, 3), conv(0, 6, 20, 3), pool(1, 20)], (3, 9, 14)),
     "one_row": ([conv(-1, 2, 4, 1), conv(0, 4, 70, 3)], (2, 1, 130)),
+    "many_channels": ([conv(-1, 3, 24, 3), conv(0, 24, 40, 3)], (3, 12, 10)),
     "deep": ([conv(-1, 3, 8, 3)] + [conv(i, 8, 8, 3) for i in range(5)] + [pool(5, 8), conv(6, 8, 8, 3)], (3, 26, 20)),
 }
 

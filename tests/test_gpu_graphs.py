@@ -138,3 +138,31 @@ def test_graph_replay_under_each_schedule(solo, asc):
             assert np.array_equal(p, base[0]) and np.array_equal(lab, base[1])
         g, r, f = ens.graph_stats()
         assert g == 1 and r == 3 and f == 0
+
+
+@pytest.mark.parametrize("n", [3, 9])
+def test_graph_and_noalloc_with_fused_blocks(n, monkeypatch):
+    """Bottleneck units always fused, beside a patch-kernel layer: replays and the no-alloc variant
+    give the eager bits (several splits of K at n = 3)."""
+    conv = lambda i, ci, co, k, res=-1: wl.Layer(op=wl.CONV2D, input=i, input2=res, c_in=ci, c_out=co, kh=k, kw=k,  # noqa: E731
+                                                 stride=1, pad=k // 2, relu=True, bn=True)
+    L = [conv(-1, 8, 512, 1), conv(0, 512, 128, 1), conv(1, 128, 128, 3), conv(2, 128, 512, 1, res=0),
+         conv(3, 512, 128, 1), conv(4, 128, 128, 3), conv(5, 128, 512, 1, res=3), conv(6, 512, 256, 3),
+         wl.Layer(op=wl.GLOBAL_AVGPOOL, input=7, c_in=256, c_out=256),
+         wl.Layer(op=wl.FC, input=8, c_in=256, c_out=10, bias=True)]
+    spec = wl.ModelSpec("blocks", L, 10, (8, 28, 28))
+    params = [wl.gen_params(spec, s, True, "random") for s in (3, 4)]
+    batch = wl.gen_images(n, spec.input_shape, "normal", True, seed=5)
+    x = torch.from_numpy(batch).to(DEV)
+    x_alt = torch.from_numpy(np.ascontiguousarray(batch[::-1])).to(DEV)
+    monkeypatch.setenv("RAFIKI_FUSED_BLOCKS", "64")
+    with envutil.create({"RAFIKI_GROUPED": "0"}, [spec] * 2, params, max_batch=n) as ens:
+        _replay_matches_eager(ens, [x, x_alt], n, [0b01, 0b11], 10)
+        ens.use_graphs(False)
+        p0, l0 = _infer(ens, x, n, 0b11, 10)
+        p = torch.empty((n, 10), dtype=torch.float32, device=DEV)
+        lab = torch.empty((n,), dtype=torch.int32, device=DEV)
+        for _ in range(2):
+            ens.infer_noalloc(x, n, 0b11, p, lab)
+            torch.cuda.synchronize()
+            assert np.array_equal(p.cpu().numpy(), p0) and np.array_equal(lab.cpu().numpy(), l0)
