@@ -2,7 +2,7 @@
 
 The host-side runtime (argument validation, the create-time dry pass, the schedulers,
 the actor-critic agent) is compiled with ``-fsanitize=address,undefined`` for the host
-pass only; device code is never instrumented.  The two kernel-only sources are linked
+pass only; device code is never instrumented.  The kernel-only sources are linked
 from the ordinary build's objects.  The result, ``_build/san/librafiki_ensemble_san.so``,
 is loaded by pointing ``RAFIKI_LIBRARY`` at it with the clang ASan runtime preloaded
 (``env_for``), since the Python interpreter itself is not instrumented.

@@ -63,11 +63,10 @@ __device__ __forceinline__ void store8(void* p, long long off, int bf16, const f
 }
 
 // ---------------------------------------------------------------- input staging
-// One thread per output pixel and 8-channel group: reads C planes (coalesced along
-// w across threads), writes one 16-byte (bf16) or 32-byte (fp32) NHWC chunk.
-// One thread per pixel and 8-channel group: x = pixels of one image, y = groups, z = images
-// from n0 on (no index is divided: at one image the launch took 6.6 us, most of it two 64-bit
-// divisions before the first load).
+// One thread per pixel and 8-channel group: reads C planes (coalesced along w across threads),
+// writes one 16-byte (bf16) or 32-byte (fp32) NHWC chunk.  Grid x = pixels of one image, y =
+// groups, z = images from n0 on: no index is divided (with two 64-bit divisions before the
+// first load the launch took 6.6 us at one image).
 __global__ void stage_images_kernel(const float* __restrict__ x, void* y, int n0, int C, int HW, int Cs, int to_bf16) {
   const int hw = blockIdx.x * blockDim.x + threadIdx.x;
   if (hw >= HW) return;
@@ -515,7 +514,6 @@ hipError_t launch_concat(const void* a, int ca, int lda, const void* b, int cb, 
 }
 
 // ---------------------------------------------------------------- fp32 direct conv
-// One thread per (pixel, output channel); taps outer, channels inner (fp32 FMA).
 // One thread per (pixel, 4 consecutive output channels).  Weights are [Kp][Co_pad]
 // (K-major), so a lane's 4 weights of one K index are one 16-byte load and the lanes
 // of a wave read consecutive ones; the input chunk is shared by the lanes of a pixel.

@@ -180,7 +180,7 @@ struct rafiki_ensemble_s {
   // prefer alone, and room on each compute unit for the other models' workgroups when
   // models run concurrently.  Every tile gives the same bits.
   std::map<int, std::vector<std::vector<int>>> tuned_lean;
-  // tuned_lean with every direct-conv choice replaced by the layer's fastest GEMM tile:
+  // tuned_lean with every direct-conv choice replaced by the layer's fastest other tile:
   // the direct kernel's persistent workgroups fill each compute unit's LDS, which leaves
   // no room for the other lane's workgroups while it runs.
   std::map<int, std::vector<std::vector<int>>> tuned_lean_gemm;
@@ -220,7 +220,7 @@ struct rafiki_ensemble_s {
   struct Sched {
     int solo = -1, ascending = 0, pa = -1, pb = -1;
     int lean = 0;   // 1: the small-map layers take their lean tiles (tuned_lean); 2: also the
-                    // solo model's direct-conv layers take their fastest GEMM tile (tuned_lean_gemm)
+                    // solo model's direct-conv layers take their fastest other tile (tuned_lean_gemm)
   };
   std::map<std::pair<int, uint32_t>, Sched> schedule;
   // Pairable models (a < b) of different layer lists: the merged op order of the two,
@@ -1183,16 +1183,6 @@ size_t partial_need(const rafiki_ensemble_s* e, const Model& M) {
   return need;
 }
 
-// The whole-network program of model M (bf16 image models only), or false if a layer
-// does not fit the kernel: convolutions 1x1 (pad 0) or 3x3 (pad 1) of stride 1 or 2
-// over 8..64 storage channels (a power of two) to at most 64 output channels, with
-// Wo a power of two, Ho * Wo a multiple of 32 and no split K at any batch size, then a
-// global average pool and the final FC over at most 64 inputs and 32 * kFusedWaves
-// classes; the layers' folded scale / shift (copied from the layer kernels' device
-// arrays, so bitwise the same) within kFusedTableBytes.  Tensors get
-// LDS offsets by liveness; a convolution whose residual is read for the last time
-// writes its output over it (each output element replaces the residual element that
-// the same lane has just read).  The plan needs at most kFusedLdsBytes.
 // LDS arena of one workgroup: live intervals, placed lowest-first (or highest-first)
 // in the first gap that fits; sizes rounded to 256 bytes.
 struct LdsArena {
