@@ -195,8 +195,8 @@ struct rafiki_ensemble_s {
   int fused_blocks = 1;
   bool chains = true;               // fp32 runs of layers in one launch (RAFIKI_CHAINS=0 at create: never)
   bool raw_input = false;           // every model's chain reads the request itself: no staging
-  std::map<int, std::vector<int>> chain_last;   // per requests of a launch (batch size times
-                                                // members) and model: last op of its chain
+  std::map<long long, std::vector<int>> chain_last;   // per requests of a launch (batch size times
+                                                      // members) and model: last op of its chain
   // RAFIKI_SMALL_TILES at create: 0 the small-tile kernel never, 1 to kNumSmallTiles that tile
   // on every layer it takes, unset (-1) the faster when tuning
   int small_tiles = -1;
@@ -1630,7 +1630,7 @@ ChainArgs plan_bands(const rafiki_ensemble_s* e, const Model& M, int last, long 
 // layer apart takes 4 us and 0.03 per term of K, or its products (storage padding included) at
 // 6 per ps if that is more.  Two layers always join: on maps of 150 to 250 columns that
 // costs up to 5 us at 1 to 8 images (35 against 30) and saves a third from 128 on (78, 116).
-int chain_ops(const rafiki_ensemble_s* e, const Model& M, int n) {
+int chain_ops(const rafiki_ensemble_s* e, const Model& M, long long n) {
   auto apart = [&](const Op& op) {
     const double px = (double)n * op.Ho * op.Wo;
     if (op.kind == O_MAXPOOL) return std::max(4.0, px * 5 * op.Cs_in * 4 / 4e6);
@@ -1930,8 +1930,8 @@ int tune(rafiki_ensemble_s* e, int n, const void* in, hipStream_t s) {
   if (e->raw_input)
     for (int k = 1; k <= kMaxGroup; ++k) {
       std::vector<int> last;
-      for (const Model& M : e->models) last.push_back(chain_ops(e, M, n * k));
-      e->chain_last[n * k] = std::move(last);
+      for (const Model& M : e->models) last.push_back(chain_ops(e, M, (long long)n * k));
+      e->chain_last[(long long)n * k] = std::move(last);
     }
   std::vector<std::vector<int>> choice(NM);
   std::vector<std::vector<std::vector<int>>> cand(NM);
@@ -2302,7 +2302,7 @@ int run_models(const rafiki_ensemble_s* e, const int* mis, int nm, const void* i
   if (nm < 1 || nm > kMaxGroup) return fail(RAFIKI_ERR_INVALID, "internal: group size");
   op_end = std::min(op_end, e->models[mis[0]].ops.size());
   const Chain& ch = e->models[mis[0]].chain;   // members of a group have the same
-  const auto cit = e->chain_last.find(n * nm);
+  const auto cit = e->chain_last.find((long long)n * nm);
   const int chain_last = !e->raw_input ? -1 : cit != e->chain_last.end() ? cit->second[mis[0]] : ch.last;
   const auto bit = e->blocks.find(n);
   const std::vector<int>* bm = nm == 1 && e->force_tile < 0 && bit != e->blocks.end() ? &bit->second[mis[0]] : nullptr;
